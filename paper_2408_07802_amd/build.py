@@ -20,7 +20,16 @@ LIB_PATH = os.path.join(HERE, "libkraken.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["gemm.hip", "attention.hip", "norm.hip", "decode.hip", "runtime.hip"]
+# (source, object name, extra flags); the large GEMM templates are compiled once per operand
+# type, in parallel
+SOURCES = [
+    *[(f"{src}.hip", f"{src}_{t}", [f"-DKRAKEN_T={t}"])
+      for src in ("gemm_tile", "gemm_mid") for t in ("f16", "bf16", "float")],
+    ("attention.hip", "attention", []), ("gemm.hip", "gemm_dispatch", []),
+    ("norm.hip", "norm", []), ("decode.hip", "decode", []), ("runtime.hip", "runtime", []),
+]
+# one relocatable object per component (the GEMM's parts are merged into gemm.o)
+OBJECTS = ["gemm", "attention", "norm", "decode", "runtime"]
 
 COMMON_FLAGS = [
     "-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}",
@@ -38,10 +47,11 @@ FILE_FLAGS = {
 }
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *COMMON_FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src),
-           "-o", obj]
+def _compile(unit) -> str:
+    src, name, extra = unit
+    obj = os.path.join(BUILD_DIR, name + ".o")
+    cmd = [HIPCC, *COMMON_FLAGS, *FILE_FLAGS.get(src, []), *extra, "-c",
+           os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{res.stdout}\n{res.stderr}")
@@ -52,7 +62,17 @@ def build(verbose: bool = False) -> str:
     """Compiles every source and links the shared library; returns its path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 4)) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        list(ex.map(_compile, SOURCES))
+    return link(verbose)
+
+
+def link(verbose: bool = False) -> str:
+    """Links the objects in BUILD_DIR into the shared library; returns its path."""
+    objs = [os.path.join(BUILD_DIR, name + ".o") for name in OBJECTS]
+    parts = [os.path.join(BUILD_DIR, n + ".o") for _, n, _ in SOURCES if n.startswith("gemm_")]
+    res = subprocess.run(["ld", "-r", *parts, "-o", objs[0]], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"merging the GEMM objects failed:\n{res.stdout}\n{res.stderr}")
     tmp = LIB_PATH + ".tmp"
     cmd = [HIPCC, "-shared", f"--offload-arch={ARCH}", "-fPIC", *objs, "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -132,16 +132,6 @@ __device__ __forceinline__ void dma16_buf(uint32_t lds_addr, i32x4 rsrc, uint32_
                : "memory", "m0");
 }
 
-// A pointer that is the same for every lane, moved to scalar registers (each half taken
-// as unsigned before widening, like dma16_off's base).
-template <typename T>
-__device__ __forceinline__ const T* uniform_ptr(const T* ptr) {
-  const uint64_t v = reinterpret_cast<uint64_t>(ptr);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-  return reinterpret_cast<const T*>(((uint64_t)hi << 32) | (uint64_t)lo);
-}
-
 // Key row read by fragment row r: bits 2 and 3 of r swapped.
 __device__ __forceinline__ int kperm(int r) {
   return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);

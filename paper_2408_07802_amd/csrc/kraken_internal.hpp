@@ -20,6 +20,17 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // input use; the compute type is the MFMA operand type of every GEMM and of attention.
 enum class DType : int { F32 = 0, BF16 = 1, F16 = 2 };
 
+// A pointer that is the same for every lane, moved to scalar registers.  (readfirstlane
+// returns a signed int: each half is taken as unsigned before widening, or a low half with
+// bit 31 set would sign-extend over the high half.)
+template <typename T>
+__device__ __forceinline__ const T* uniform_ptr(const T* ptr) {
+  const uint64_t v = reinterpret_cast<uint64_t>(ptr);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+  return reinterpret_cast<const T*>(((uint64_t)hi << 32) | (uint64_t)lo);
+}
+
 inline size_t dtype_size(DType t) { return t == DType::F32 ? 4 : 2; }
 
 template <typename S>
@@ -53,7 +64,10 @@ enum GemmEpi : int {
   EPI_BIAS_N = 0,       // C (storage type) = acc + bias[n]
   EPI_BIAS_N_GELU = 1,  // C (storage type) = GELU(acc + bias[n]), exact erf form
   EPI_BIAS_N_RES = 2,   // C (float32)      = acc + bias[n] + R[m][n]   (bias, R optional)
-  EPI_BIAS_M = 3        // C (storage type) = acc + bias[m]
+  EPI_BIAS_M = 3,       // C (storage type) = acc + bias[m]
+  EPI_BIAS_N_HILO = 4,  // v = acc + bias[n] + R[m][n] as two 16-bit terms: C = S(v), and
+                        // S(v - S(v)) sPlane elements further
+  EPI_PART = 5          // C (float32)      = acc of one K split, plane sp at C + sp * sPlane
 };
 
 // C[z][m][n] = epi( sum_g sum_k A[z][g][m][k] * B[z][g mod gBmod][n][k] )
@@ -74,12 +88,41 @@ struct GemmDesc {
   int kgroups;
   int64_t gA, gB;
   int gBmod;
+  // EPI_PART: number of K splits and the elements between their planes; EPI_BIAS_N_HILO:
+  // elements from the high to the low terms
+  int splits;
+  int64_t sPlane;
   // fp16 outputs only: set to 1 (vector store) when a finite fp32 result rounds to an
   // fp16 infinity (|v| >= 65520); NULL: no check
   int* ovf;
 };
 
 hipError_t launch_gemm(const GemmDesc& g, hipStream_t s);
+
+// Kernel and tile of a GEMM.
+enum class GemmKind : int { TILE256, TILE128, MID, SKINNY };
+struct GemmPlan {
+  GemmKind kind;
+  int nb;       // MID: 32-column blocks per tile
+  int splits;   // K splits
+};
+// Plan of a GEMM of type dt.  part_elems: fp32 elements available for K-split partial planes
+// (0: no split; only EPI_BIAS_N_RES results can be split).
+// Only results that the caller sums itself (see PartSum) may be given part_elems > 0.
+GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
+                   int64_t part_elems);
+hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStream_t s);
+// The kernels of the plans TILE256 / TILE128 and MID (one object file per operand type).
+template <typename S>
+hipError_t launch_gemm_tile(const GemmDesc& g, bool big, hipStream_t s);
+template <typename S>
+hipError_t launch_gemm_mid(const GemmDesc& g, int nb, hipStream_t s);
+template <> hipError_t launch_gemm_tile<bf16>(const GemmDesc&, bool, hipStream_t);
+template <> hipError_t launch_gemm_tile<f16>(const GemmDesc&, bool, hipStream_t);
+template <> hipError_t launch_gemm_tile<float>(const GemmDesc&, bool, hipStream_t);
+template <> hipError_t launch_gemm_mid<bf16>(const GemmDesc&, int, hipStream_t);
+template <> hipError_t launch_gemm_mid<f16>(const GemmDesc&, int, hipStream_t);
+template <> hipError_t launch_gemm_mid<float>(const GemmDesc&, int, hipStream_t);
 
 // Causal flash attention over packed sequences; n_kv_heads key/value heads (query head
 // h reads head h / (n_heads / n_kv_heads)), dkv = n_kv_heads * hd.
@@ -104,18 +147,43 @@ inline int vt_ld(int T) { return (T + 63) & ~63; }
 hipError_t launch_zero_cols(DType dt, void* base, int64_t rows, int64_t ld, int c0, int c1,
                             hipStream_t s);
 
+// A GEMM result left as partial planes, to be summed by the kernel that reads it:
+// v[i][t][c] = sum_s part[s * plane + (i T + t) d + c] + bias[i d + c] + bias2[i d + c]
+//              + res[i * res_stride + t d + c]     (s < splits; bias, bias2, res may be NULL)
+// splits = 0: nothing to sum.  out (if not NULL) receives v, [n][T][d] fp32.
+struct PartSum {
+  const float* part = nullptr;
+  int splits = 0;
+  int64_t plane = 0;
+  const float* bias = nullptr;
+  const float* bias2 = nullptr;
+  const float* res = nullptr;
+  int64_t res_stride = 0;
+  float* out = nullptr;
+};
+
 // LayerNorm of n rows-sets: out[i][t] = LN(x[i*xs + t*d]) with per-i gamma/beta.  Rows are
 // d wide (the stored width); the statistics cover the first dl (logical width, a multiple
 // of 4; padding columns past it hold zeros and have gamma = beta = 0).
 // ovf (fp16 outputs; may be NULL): set to 1 when an output overflows the fp16 range.
+// ps.splits > 0: the rows are ps's sum (and go to ps.out) instead of x.
 hipError_t launch_layernorm(DType dt, const float* x, int64_t x_batch_stride, const float* gamma,
                             const float* beta, void* out, int n, int T, int d, int dl, float eps,
-                            int* ovf, hipStream_t s);
+                            int* ovf, hipStream_t s, const PartSum& ps = PartSum());
 
 // out[i][t] = LN(h[i][t] + y[t]); y = shared[t] or sum_k x[k][t].  d, dl, ovf as for LN1.
+// ps.splits > 0: h is ps's sum (and goes to ps.out).
 hipError_t launch_combine_ln2(DType dt, const float* x, const float* shared, const float* h,
                               const float* gamma, const float* beta, void* out, int n, int T,
-                              int d, int dl, float eps, int* ovf, hipStream_t s);
+                              int d, int dl, float eps, int* ovf, hipStream_t s,
+                              const PartSum& ps = PartSum());
+
+// v = ps's sum (with splits = 0: bias and res alone) over n x T rows of d elements, written as
+// fp32 to ps.out with row stride out_ld (NULL: not), and as the two 16-bit terms hi = S(v) at
+// hilo and lo = S(v - hi) at hilo + n T d (NULL: not; dt then names S).  ovf as for LN1 (a hi
+// term that overflows fp16).
+hipError_t launch_finish(DType dt, const PartSum& ps, int n, int T, int d, int64_t out_ld,
+                         void* hilo, int* ovf, hipStream_t s);
 
 // dst[r * dst_ld + pad(c)] = float(src[r * src_ld + c]) for r < R, c < C, with
 // pad(c) = (c / g) * gp + c % g (logical element c of group c / g, placed in a group of gp
@@ -138,11 +206,6 @@ hipError_t launch_gather_rows(const float* src, const int* rows, float* dst, int
 
 // dst[k] = float(src[k]) for k < count.
 hipError_t launch_to_f32(DType dt, const void* src, float* dst, int64_t count, hipStream_t s);
-
-// Two-term split of fp32 values in a 16-bit type: hi = S(v), lo = S(v - hi);
-// hi at dst, lo at dst + count (elements).  ovf as for LN1 (a hi part that overflows fp16).
-hipError_t launch_split16(DType dt, const float* src, void* dst, int64_t count, int* ovf,
-                          hipStream_t s);
 
 // dst[pad_c(c)][pad_r(r)] = Dst(src[r*src_ld + c]) for r < R, c < C, dst row stride dst_ld,
 // with pad_r(r) = (r / gr) * grp + r % gr and pad_c likewise with (gc, gcp) (see

@@ -10,6 +10,7 @@
 // so each HBM byte is touched once.  Rows are read as float4, statistics are
 // kept in fp32 with a two-pass (mean, then centred variance) reduction.
 #include <algorithm>
+#include <type_traits>
 
 #include "kraken_internal.hpp"
 
@@ -124,6 +125,22 @@ inline int vecs_for(int d) {
   return v <= 1 ? 1 : v <= 2 ? 2 : v <= 4 ? 4 : v <= 8 ? 8 : MAX_VEC;
 }
 
+// Calls fn(vecs, part) with the compile-time float4s per thread and PART of a launch.
+template <class Fn>
+void by_vecs(int d, bool part, Fn&& fn) {
+  auto with = [&](auto V) {
+    if (part) fn(V, std::true_type{});
+    else fn(V, std::false_type{});
+  };
+  switch (vecs_for(d)) {
+    case 1: with(std::integral_constant<int, 1>{}); break;
+    case 2: with(std::integral_constant<int, 2>{}); break;
+    case 4: with(std::integral_constant<int, 4>{}); break;
+    case 8: with(std::integral_constant<int, 8>{}); break;
+    default: with(std::integral_constant<int, MAX_VEC>{}); break;
+  }
+}
+
 // Number of float4s this thread owns in a row of d floats.
 __device__ __forceinline__ int my_vecs(int d) {
   const int nv4 = d / 4;
@@ -131,12 +148,48 @@ __device__ __forceinline__ int my_vecs(int d) {
   return tid < nv4 ? (nv4 - tid + NORM_THREADS - 1) / NORM_THREADS : 0;
 }
 
+__device__ __forceinline__ void add4(float4& a, float4 b) {
+  a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+}
+
+// Four elements of a PartSum: row element `at` = (i T + t) d + c of the planes, element
+// i d + c of the biases, res_at = i * res_stride + t d + c of the residual.
+__device__ __forceinline__ float4 part_sum4(const PartSum& ps, int64_t at, int64_t bias_at,
+                                            int64_t res_at) {
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s = 0; s < ps.splits; ++s)
+    add4(a, *reinterpret_cast<const float4*>(ps.part + s * ps.plane + at));
+  if (ps.bias) add4(a, *reinterpret_cast<const float4*>(ps.bias + bias_at));
+  if (ps.bias2) add4(a, *reinterpret_cast<const float4*>(ps.bias2 + bias_at));
+  if (ps.res) add4(a, *reinterpret_cast<const float4*>(ps.res + res_at));
+  return a;
+}
+
+// This thread's float4s of row (i, t): ps's sum (stored to ps.out) or the row at `row`.
+template <int V, bool PART>
+__device__ __forceinline__ void load_row(float4* v, int nv, const float* row, const PartSum& ps,
+                                         int i, int t, int T, int d) {
+#pragma unroll
+  for (int u = 0; u < V; ++u) {
+    if (u >= nv) break;
+    const int c = (threadIdx.x + u * NORM_THREADS) * 4;
+    if constexpr (PART) {
+      const int64_t at = ((int64_t)i * T + t) * d + c;
+      v[u] = part_sum4(ps, at, (int64_t)i * d + c, i * ps.res_stride + (int64_t)t * d + c);
+      *reinterpret_cast<float4*>(ps.out + at) = v[u];
+    } else {
+      v[u] = *reinterpret_cast<const float4*>(row + c);
+    }
+  }
+}
+
 // V: float4s per thread that the launch's d needs at most (registers are sized by it).
-template <typename S, int V>
+// PART: the rows are ps's sum.  (As a run-time choice it made a one-row launch 0.5 us longer.)
+template <typename S, int V, bool PART>
 __global__ __launch_bounds__(NORM_THREADS) void layernorm_kernel(
     const float* __restrict__ x, int64_t xs, const float* __restrict__ gamma,
     const float* __restrict__ beta, S* __restrict__ out, int n, int T, int d, int dl, float eps,
-    int* __restrict__ ovf) {
+    int* __restrict__ ovf, PartSum ps) {
   __shared__ float red[NORM_THREADS / 64];
   const int t = blockIdx.x;
   const int nv = my_vecs(d);
@@ -148,10 +201,7 @@ __global__ __launch_bounds__(NORM_THREADS) void layernorm_kernel(
   float mean = 0.f, rstd = 0.f;
   for (int i = i0; i < i1; ++i) {
     if (i == i0 || xs != 0) {
-      const float* row = x + i * xs + (int64_t)t * d;
-#pragma unroll
-      for (int u = 0; u < V; ++u)
-        if (u < nv) v[u] = *reinterpret_cast<const float4*>(row + (threadIdx.x + u * NORM_THREADS) * 4);
+      load_row<V, PART>(v, nv, x + i * xs + (int64_t)t * d, ps, i, t, T, d);
       row_stats<V>(v, nv, dl, eps, red, mean, rstd);
     }
     amax = fmaxf(amax, ln_write<S, V>(v, nv, mean, rstd, gamma + (int64_t)i * d,
@@ -160,11 +210,11 @@ __global__ __launch_bounds__(NORM_THREADS) void layernorm_kernel(
   flag_overflow<S>(amax, ovf);
 }
 
-template <typename S, int V>
+template <typename S, int V, bool PART>
 __global__ __launch_bounds__(NORM_THREADS) void combine_ln2_kernel(
     const float* __restrict__ x, const float* __restrict__ shared, const float* __restrict__ h,
     const float* __restrict__ gamma, const float* __restrict__ beta, S* __restrict__ out, int n,
-    int T, int d, int dl, float eps, int* __restrict__ ovf) {
+    int T, int d, int dl, float eps, int* __restrict__ ovf, PartSum ps) {
   __shared__ float red[NORM_THREADS / 64];
   float amax = 0.f;
   const int t = blockIdx.x;
@@ -191,13 +241,10 @@ __global__ __launch_bounds__(NORM_THREADS) void combine_ln2_kernel(
   const int i1 = (int)((int64_t)n * (blockIdx.y + 1) / gridDim.y);
   for (int i = i0; i < i1; ++i) {
     float4 v[V];
-    const float* hrow = h + i * plane + (int64_t)t * d;
+    load_row<V, PART>(v, nv, h + i * plane + (int64_t)t * d, ps, i, t, T, d);
 #pragma unroll
-    for (int u = 0; u < V; ++u) {
-      if (u >= nv) break;
-      const float4 a = *reinterpret_cast<const float4*>(hrow + (threadIdx.x + u * NORM_THREADS) * 4);
-      v[u] = make_float4(a.x + y[u].x, a.y + y[u].y, a.z + y[u].z, a.w + y[u].w);
-    }
+    for (int u = 0; u < V; ++u)
+      if (u < nv) add4(v[u], y[u]);
     float mean, rstd;
     row_stats<V>(v, nv, dl, eps, red, mean, rstd);
     amax = fmaxf(amax, ln_write<S, V>(v, nv, mean, rstd, gamma + (int64_t)i * d,
@@ -220,17 +267,28 @@ __global__ void scale_kernel(S* __restrict__ p, int64_t count, float c) {
     p[k] = (S)((float)p[k] * c);
 }
 
+// launch_finish: each thread takes four elements at a time (row-major over n x T rows).
 template <typename S>
-__global__ void split16_kernel(const float* __restrict__ src, S* __restrict__ dst, int64_t count,
-                               int* __restrict__ ovf) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+__global__ __launch_bounds__(256) void finish_kernel(PartSum ps, int64_t rows, int T, int d,
+                                                     int64_t out_ld, S* __restrict__ hilo,
+                                                     int* __restrict__ ovf) {
+  const int d4 = d / 4;
+  const int64_t total = rows * d4, stride = (int64_t)gridDim.x * 256;
   float amax = 0.f;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < count; k += stride) {
-    const float v = src[k];
-    const S hi = (S)v;
-    dst[k] = hi;
-    dst[k + count] = (S)(v - (float)hi);
-    amax = fmaxf(amax, fabsf(v));
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < total; k += stride) {
+    const int64_t r = k / d4;
+    const int c = (int)(k - r * d4) * 4;
+    const int64_t i = r / T, t = r - i * T, at = r * d + c;
+    const float4 v = part_sum4(ps, at, i * d + c, i * ps.res_stride + t * d + c);
+    if (ps.out) *reinterpret_cast<float4*>(ps.out + r * out_ld + c) = v;
+    if constexpr (sizeof(S) == 2) {
+      if (hilo) {
+        store4(hilo + at, v.x, v.y, v.z, v.w);
+        store4(hilo + rows * d + at, v.x - (float)(S)v.x, v.y - (float)(S)v.y,
+               v.z - (float)(S)v.z, v.w - (float)(S)v.w);
+        amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+      }
+    }
   }
   flag_overflow<S>(amax, ovf);
 }
@@ -361,7 +419,7 @@ unsigned sub_groups(int n, int T) {
 
 hipError_t launch_layernorm(DType dt, const float* x, int64_t xs, const float* gamma,
                             const float* beta, void* out, int n, int T, int d, int dl, float eps,
-                            int* ovf, hipStream_t s) {
+                            int* ovf, hipStream_t s, const PartSum& ps) {
   if (T <= 0 || n <= 0) return hipSuccess;
   if (d % 4 != 0 || d > NORM_THREADS * MAX_VEC * 4 || dl % 4 != 0 || dl < 4 || dl > d)
     return hipErrorInvalidValue;
@@ -371,20 +429,18 @@ hipError_t launch_layernorm(DType dt, const float* x, int64_t xs, const float* g
     // a shared input row keeps its statistics in one workgroup per token
     const dim3 grid(T, xs != 0 ? (unsigned)n : sub_groups(n, T)), block(NORM_THREADS);
     S* o = static_cast<S*>(out);
-    switch (vecs_for(d)) {
-      case 1: hipLaunchKernelGGL((layernorm_kernel<S, 1>), grid, block, 0, s, x, xs, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      case 2: hipLaunchKernelGGL((layernorm_kernel<S, 2>), grid, block, 0, s, x, xs, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      case 4: hipLaunchKernelGGL((layernorm_kernel<S, 4>), grid, block, 0, s, x, xs, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      case 8: hipLaunchKernelGGL((layernorm_kernel<S, 8>), grid, block, 0, s, x, xs, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      default: hipLaunchKernelGGL((layernorm_kernel<S, MAX_VEC>), grid, block, 0, s, x, xs, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-    }
+    by_vecs(d, ps.splits > 0, [&](auto V, auto P) {
+      hipLaunchKernelGGL((layernorm_kernel<S, decltype(V)::value, decltype(P)::value>), grid, block, 0, s,
+                         x, xs, gamma, beta, o, n, T, d, dl, eps, ovf, ps);
+    });
     return hipGetLastError();
   });
 }
 
 hipError_t launch_combine_ln2(DType dt, const float* x, const float* shared, const float* h,
                               const float* gamma, const float* beta, void* out, int n, int T,
-                              int d, int dl, float eps, int* ovf, hipStream_t s) {
+                              int d, int dl, float eps, int* ovf, hipStream_t s,
+                              const PartSum& ps) {
   if (T <= 0 || n <= 0) return hipSuccess;
   if (d % 4 != 0 || d > NORM_THREADS * MAX_VEC * 4 || dl % 4 != 0 || dl < 4 || dl > d)
     return hipErrorInvalidValue;
@@ -392,13 +448,10 @@ hipError_t launch_combine_ln2(DType dt, const float* x, const float* shared, con
     using S = decltype(tag);
     const dim3 grid(T, sub_groups(n, T)), block(NORM_THREADS);
     S* o = static_cast<S*>(out);
-    switch (vecs_for(d)) {
-      case 1: hipLaunchKernelGGL((combine_ln2_kernel<S, 1>), grid, block, 0, s, x, shared, h, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      case 2: hipLaunchKernelGGL((combine_ln2_kernel<S, 2>), grid, block, 0, s, x, shared, h, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      case 4: hipLaunchKernelGGL((combine_ln2_kernel<S, 4>), grid, block, 0, s, x, shared, h, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      case 8: hipLaunchKernelGGL((combine_ln2_kernel<S, 8>), grid, block, 0, s, x, shared, h, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-      default: hipLaunchKernelGGL((combine_ln2_kernel<S, MAX_VEC>), grid, block, 0, s, x, shared, h, gamma, beta, o, n, T, d, dl, eps, ovf); break;
-    }
+    by_vecs(d, ps.splits > 0, [&](auto V, auto P) {
+      hipLaunchKernelGGL((combine_ln2_kernel<S, decltype(V)::value, decltype(P)::value>), grid, block, 0, s,
+                         x, shared, h, gamma, beta, o, n, T, d, dl, eps, ovf, ps);
+    });
     return hipGetLastError();
   });
 }
@@ -435,18 +488,18 @@ hipError_t launch_zero_cols(DType dt, void* base, int64_t rows, int64_t ld, int 
   });
 }
 
-hipError_t launch_split16(DType dt, const float* src, void* dst, int64_t count, int* ovf,
-                          hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  if (dt == DType::BF16)
-    hipLaunchKernelGGL(split16_kernel<bf16>, dim3(grid_for(count)), dim3(256), 0, s, src,
-                       static_cast<bf16*>(dst), count, ovf);
-  else if (dt == DType::F16)
-    hipLaunchKernelGGL(split16_kernel<f16>, dim3(grid_for(count)), dim3(256), 0, s, src,
-                       static_cast<f16*>(dst), count, ovf);
-  else
+hipError_t launch_finish(DType dt, const PartSum& ps, int n, int T, int d, int64_t out_ld,
+                         void* hilo, int* ovf, hipStream_t s) {
+  const int64_t rows = (int64_t)n * T;
+  if (rows <= 0) return hipSuccess;
+  if (d < 4 || d % 4 != 0 || out_ld % 4 != 0 || (hilo && dt == DType::F32))
     return hipErrorInvalidValue;
-  return hipGetLastError();
+  return by_type(dt, [&](auto tag) {
+    using S = decltype(tag);
+    hipLaunchKernelGGL(finish_kernel<S>, dim3(grid_for(rows * (d / 4))), dim3(256), 0, s, ps, rows,
+                       T, d, out_ld, static_cast<S*>(hilo), ovf);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_transpose(DType src_t, const void* src, int64_t src_ld, DType dst_t, void* dst,

@@ -179,6 +179,8 @@ struct kraken_model {
   // workspace (stored widths)
   float *X32 = nullptr, *xbuf = nullptr, *hbuf = nullptr;
   void *act = nullptr, *qk = nullptr, *vt = nullptr, *o = nullptr, *g = nullptr;
+  float* part = nullptr;             // partial planes of K-split GEMMs
+  int64_t part_elems = 0;
   char* ws_end = nullptr;
   // KRAKEN_DEBUG_SYNC=1 at kraken_create: synchronise and check after every launch
   bool debug_sync = false;
@@ -362,6 +364,11 @@ size_t carve_weights(kraken_model* m, void* base) {
   return c.off;
 }
 
+// Most fp32 elements of a model's partial planes.  The largest measured gain of a split that
+// needs nearly as many: W_concat of four sub-layers of width 1280 over 17228 tokens, 457 us
+// whole and 383 us in two planes (44 million elements).
+constexpr size_t PART_MAX_ELEMS = 64u << 20;
+
 size_t carve_workspace(kraken_model* m, void* base) {
   Carver c(base);
   const Dims& D = m->D;
@@ -378,6 +385,9 @@ size_t carve_workspace(kraken_model* m, void* base) {
   m->act = c.take(N * T * dp * es);
   m->qk = c.take(N * T * (dq + dkv) * es);
   m->o = c.take(N * T * std::max(dq, dkv) * es);
+  // Planes of K-split GEMMs (see plan_gemm): up to 8 of the widest result, at most 256 MB
+  m->part_elems = (int64_t)std::min<size_t>(8 * N * T * dp, PART_MAX_ELEMS);
+  m->part = (float*)c.take(m->part_elems * sizeof(float));
   // vt and g stay adjacent and last: a decode step keeps its attention partials there
   m->vt = c.take(N * dkv * (size_t)vt_ld(m->Tmax) * es);
   m->g = c.take(std::max(N * T * Fp, 2 * N * T * dp) * es);
@@ -522,15 +532,38 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   if (!decode && ldv > T)
     RUN(KRAKEN_K_OTHER, launch_zero_cols(dt, m->vt, N * dkv, ldv, T, ldv, s), "V padding");
 
+  // The output and FFN-down projections have few columns and a long reduction; where that
+  // leaves CUs idle their reduction is split (plan_gemm), and the kernel that reads the result
+  // sums the planes: LN2 for h, the next LN1 (or, after the last layer, launch_finish) for x.
+  // The parallel layer has no kernel that reads h alone: its two projections are split
+  // together and their planes summed as one, or neither is.
+  const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
+  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N,
+                              parallel ? m->part_elems / 2 : m->part_elems);
+  GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N,
+                              parallel ? m->part_elems / 2 : m->part_elems);
+  if (parallel && plan_o.splits > 1 && plan_d.splits == 1)
+    plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, 0);
+  const bool part_d = plan_d.splits > 1;
+  const bool part_o = parallel ? part_d : plan_o.splits > 1;
+  const int64_t plane = N * Td;
+  PartSum xsum;                       // the previous layer's x, if it is still in planes
+  // W_concat's 16-bit operand: x = hi + lo, written by the last FFN-down projection itself
+  // where it is not split and nobody wants x
+  const bool wcat16 = D.arch == KRAKEN_ARCH_KRAKEN && dt != DType::F32;
+  const bool hilo_epi = wcat16 && !part_d && !sub_out;
+
   for (int j = 0; j < m->L; ++j) {
     const LayerW& w = m->layers[j];
+    const bool last = j + 1 == m->L;
     const float* xin = j == 0 ? X32 : m->xbuf;   // sub-layer inputs x_i
     const int64_t xs = j == 0 ? 0 : Td;           // first layer: one shared input
     char* cache_j = kv ? kv->cache + (size_t)j * kv->layer_bytes : nullptr;
     RUN(KRAKEN_K_LN1,
         launch_layernorm(dt, xin, xs, w.ln1_g, w.ln1_b, m->act, (int)N, T, (int)dp, (int)d,
-                         m->eps, ovf, s),
+                         m->eps, ovf, s, xsum),
         "ln1");
+    PartSum hsum;
     {
       GemmDesc g = gemm_base(dt);
       g.epi = EPI_BIAS_N;
@@ -598,19 +631,26 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       g.bias = w.bo; g.sBias = dp;
       g.R = xin; g.sR = xs;
       g.M = T; g.N = (int)dp; g.K = (int)dq; g.batch = (int)N;
-      RUN(KRAKEN_K_GEMM_O, launch_gemm(g, s), "output projection");
+      if (part_o) {
+        g.epi = EPI_PART;
+        g.C = m->part;
+        g.splits = plan_o.splits; g.sPlane = plane;
+        hsum.part = m->part; hsum.splits = plan_o.splits; hsum.plane = plane;
+        hsum.bias = w.bo; hsum.res = xin; hsum.res_stride = xs; hsum.out = m->hbuf;
+      }
+      RUN(KRAKEN_K_GEMM_O, launch_gemm_planned(g, plan_o, s), "output projection");
     }
     // The FFN's LayerNorm: Kraken reads h + y with y the combine (Algorithm 1); the
     // GPT-like layer reads h; the parallel layer's FFN takes the LN1 output still in act.
     if (D.arch == KRAKEN_ARCH_KRAKEN)
       RUN(KRAKEN_K_COMBINE,
           launch_combine_ln2(dt, m->xbuf, j == 0 ? X32 : nullptr, m->hbuf, w.ln2_g, w.ln2_b,
-                             m->act, (int)N, T, (int)dp, (int)d, m->eps, ovf, s),
+                             m->act, (int)N, T, (int)dp, (int)d, m->eps, ovf, s, hsum),
           "combine + ln2");
     else if (D.arch == KRAKEN_ARCH_GPT)
       RUN(KRAKEN_K_COMBINE,
           launch_layernorm(dt, m->hbuf, Td, w.ln2_g, w.ln2_b, m->act, (int)N, T, (int)dp, (int)d,
-                           m->eps, ovf, s),
+                           m->eps, ovf, s, hsum),
           "ln2");
     {
       GemmDesc g = gemm_base(dt);
@@ -632,8 +672,50 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       g.bias = w.b2; g.sBias = dp;
       g.R = m->hbuf; g.sR = Td;
       g.M = T; g.N = (int)dp; g.K = (int)Fp; g.batch = (int)N;
-      RUN(KRAKEN_K_GEMM_DOWN, launch_gemm(g, s), "FFN down");
+      if (part_d) {
+        g.epi = EPI_PART;
+        g.splits = plan_d.splits; g.sPlane = plane;
+        if (parallel) {
+          // x = xin + O planes + FFN planes + bo + b2
+          g.C = m->part + plan_o.splits * plane;
+          xsum = hsum;
+          xsum.splits += plan_d.splits;
+          xsum.bias2 = w.b2;
+        } else {
+          g.C = m->part;
+          xsum.part = m->part; xsum.splits = plan_d.splits; xsum.plane = plane;
+          xsum.bias = w.b2; xsum.res = m->hbuf; xsum.res_stride = Td;
+        }
+        xsum.out = m->xbuf;
+      } else if (last && hilo_epi) {
+        g.epi = EPI_BIAS_N_HILO;       // hi and lo take the place of x, 2 x 2 bytes for 4
+        g.sPlane = N * Td;
+        g.ovf = ovf;
+      }
+      RUN(KRAKEN_K_GEMM_DOWN, launch_gemm_planned(g, plan_d, s), "FFN down");
     }
+  }
+
+  // After the last layer: sum x's planes, split x for W_concat, or both.  A GPT-like or
+  // parallel stack's x goes straight to hidden_out when nothing else needs it.
+  const void* hilo = hilo_epi ? static_cast<const void*>(m->xbuf) : m->g;
+  bool out_done = false;
+  if (part_d || (wcat16 && !hilo_epi)) {
+    PartSum ps = xsum;
+    if (!part_d) {
+      ps.res = m->xbuf;
+      ps.res_stride = Td;
+    }
+    ps.out = !part_d || (wcat16 && !sub_out) ? nullptr : m->xbuf;
+    int64_t ld = dp;
+    if (D.arch != KRAKEN_ARCH_KRAKEN && hidden_out && !sub_out && !final_rows && d == dp) {
+      ps.out = hidden_out;
+      ld = d;
+      out_done = true;
+    }
+    RUN(wcat16 ? KRAKEN_K_CONCAT : KRAKEN_K_OTHER,
+        launch_finish(dt, ps, (int)N, T, (int)dp, ld, wcat16 ? m->g : nullptr, ovf, s),
+        "sum of the FFN planes");
   }
 
   if (sub_out)
@@ -651,9 +733,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     g.epi = EPI_BIAS_N_RES;
     if (dt != DType::F32) {
       // 16-bit operands: Y = hi + lo with hi = S(Y), lo = S(Y - hi); 2N groups
-      RUN(KRAKEN_K_CONCAT, launch_split16(dt, m->xbuf, m->g, N * Td, ovf, s),
-          "W_concat operand split");
-      g.A = m->g;
+      g.A = hilo;
       g.kgroups = (int)(2 * N);
     } else {
       g.A = m->xbuf;
@@ -668,13 +748,27 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     } else {
       g.C = hidden_out; g.ldc = (int)d; g.N = (int)d;
     }
-    RUN(KRAKEN_K_CONCAT, launch_gemm(g, s), "W_concat");
+    const GemmPlan plan = plan_gemm(dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, m->part_elems);
+    if (plan.splits > 1) {
+      PartSum ps;
+      ps.part = m->part; ps.splits = plan.splits; ps.plane = (int64_t)T * g.N;
+      ps.out = static_cast<float*>(g.C);
+      g.epi = EPI_PART;
+      g.C = m->part;
+      g.splits = plan.splits; g.sPlane = ps.plane;
+      g.ldc = g.N;
+      RUN(KRAKEN_K_CONCAT, launch_gemm_planned(g, plan, s), "W_concat");
+      RUN(KRAKEN_K_CONCAT, launch_finish(DType::F32, ps, 1, T, g.N, g.N, nullptr, nullptr, s),
+          "sum of the W_concat planes");
+    } else {
+      RUN(KRAKEN_K_CONCAT, launch_gemm_planned(g, plan, s), "W_concat");
+    }
     if (final_rows && hidden_out)
       RUN(KRAKEN_K_OTHER,
           hipMemcpy2DAsync(hidden_out, d * sizeof(float), fin, dp * sizeof(float),
                            d * sizeof(float), T, hipMemcpyDeviceToDevice, s),
           "output copy");
-  } else if (hidden_out) {
+  } else if (hidden_out && !out_done) {
     // the GPT-like and parallel stacks end with their last layer's output
     RUN(KRAKEN_K_OTHER,
         hipMemcpy2DAsync(hidden_out, d * sizeof(float), fin, dp * sizeof(float),

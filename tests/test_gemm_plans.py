@@ -1,0 +1,112 @@
+"""GEMM plans: the planner's rules (host) and every kernel, tile and epilogue a plan can name,
+forced at the edges of its tiles (GPU, against fp64 products of the same operands)."""
+
+import ctypes
+import math
+import random
+
+import pytest
+import torch
+
+F32, BF16, F16 = 0, 1, 2
+BIAS_N, GELU, RES, BIAS_M, HILO, PART = range(6)
+TILE256, TILE128, MID, SKINNY = range(4)
+P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+
+
+class Desc(ctypes.Structure):       # kraken::GemmDesc
+    _fields_ = [("dt", I), ("epi", I), ("A", P), ("B", P), ("C", P), ("bias", P), ("R", P),
+                ("M", I), ("N", I), ("K", I), ("lda", I), ("ldb", I), ("ldc", I), ("sA", L),
+                ("sB", L), ("sC", L), ("sR", L), ("sBias", L), ("batch", I), ("kgroups", I),
+                ("gA", L), ("gB", L), ("gBmod", I), ("splits", I), ("sPlane", L), ("ovf", P)]
+
+
+class Plan(ctypes.Structure):       # kraken::GemmPlan
+    _fields_ = [("kind", I), ("nb", I), ("splits", I)]
+
+
+def _lib():
+    from paper_2408_07802_amd import kraken
+    return kraken.lib()
+
+
+def plan(dt, epi, M, N, K, kgroups, batch, part):
+    f = getattr(_lib(), "_ZN6kraken9plan_gemmENS_5DTypeEiiiiiil")
+    f.argtypes, f.restype = [I] * 7 + [L], Plan
+    return f(dt, epi, M, N, K, kgroups, batch, part)
+
+
+def test_plans_stay_within_their_limits():
+    rng = random.Random(3)
+    for _ in range(4000):
+        dt = rng.choice([F32, BF16, F16])
+        M = int(math.exp(rng.uniform(0, math.log(20000))))
+        N, K = 4 * rng.randint(1, 4096), 64 * rng.randint(1, 256)
+        g, b = rng.choice([1, 1, 2, 16]), rng.choice([1, 2, 4, 8])
+        part = rng.choice([0, M * N * b, 5 * M * N * b, 1 << 40])
+        p = plan(dt, RES, M, N, K, g, b, part)
+        assert (p.kind == SKINNY) == (M <= 64 and dt != F32)
+        assert p.kind != MID or 1 <= p.nb <= 6
+        slices = K // (32 if dt == F32 else 64) * g
+        assert 1 <= p.splits <= 8 and (p.splits == 1 or 2 * p.splits <= slices)
+        assert p.splits == 1 or p.splits * M * N * b <= part
+
+
+def test_large_prompts_keep_their_rows_independent_of_the_length():
+    # the benchmark layer at 4096 and 8192 tokens: whole reductions either way, so a prefix
+    # gives the same bits
+    for M in (4096, 8192):
+        for N, K in ((4096, 2048), (2048, 2048), (8192, 2048), (2048, 8192)):
+            assert plan(F16, RES, M, N, K, 1, 8, 1 << 26).splits == 1
+
+
+# (M, N, K, batch, K splits): one row past and short of tiles of 128 and 256, column counts
+# that are no multiple of a tile or of 4, splits of unequal length, a single slice
+SHAPES = [(65, 96, 64, 1, 1), (127, 130, 192, 2, 3), (128, 160, 128, 1, 2), (129, 257, 320, 2, 5),
+          (255, 64, 640, 1, 4), (257, 320, 512, 2, 8), (300, 33, 448, 3, 2)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("epi", [BIAS_N, GELU, RES, BIAS_M, HILO, PART])
+@pytest.mark.parametrize("dt", [F32, BF16, F16])
+def test_every_plan_at_tile_edges(dt, epi):
+    if epi == HILO and dt == F32:
+        pytest.skip("two 16-bit terms")
+    f = getattr(_lib(), "_ZN6kraken19launch_gemm_plannedERKNS_8GemmDescERKNS_8GemmPlanEP12ihipStream_t")
+    f.restype = I
+    S = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[dt]
+    out = torch.float32 if epi in (RES, PART) else S
+    # rounding of the stored type (half a unit, and twice that for ties of fp32 sums); fp32
+    # sums of K products of unit-variance operands: far below 1e-5 of the result's norm
+    tol = {torch.float32: 1e-5, torch.float16: 4e-4, torch.bfloat16: 3.2e-3}[out]
+    if epi == HILO:
+        tol = {BF16: 2e-5, F16: 1e-6}[dt]     # (2^-8)^2, and (2^-11)^2 with fp32 sums
+    plans = [(TILE256, 0), (TILE128, 0)] + [(MID, nb) for nb in range(1, 7)]
+    for M, N, K, batch, splits in SHAPES:
+        if epi == HILO and N % 4:
+            N += 4 - N % 4
+        g = torch.Generator(device="cuda").manual_seed(M + N + K)
+        A = torch.randn((batch, M, K), generator=g, device="cuda").to(S)
+        B = (torch.randn((batch, N, K), generator=g, device="cuda") / math.sqrt(K)).to(S)
+        bias = torch.randn((batch, M if epi == BIAS_M else N), generator=g, device="cuda")
+        R = torch.randn((batch, M, N), generator=g, device="cuda")
+        ref = torch.stack([a @ b.T for a, b in zip(A.double(), B.double())])
+        if epi != PART:
+            ref = ref + (bias.double()[:, :, None] if epi == BIAS_M else bias.double()[:, None])
+        if epi == GELU:
+            ref = torch.nn.functional.gelu(ref)
+        if epi in (RES, HILO):
+            ref = ref + R.double()
+        planes = splits if epi == PART else 2 if epi == HILO else 1
+        d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
+                 K, K, N, M * K, N * K, M * N, M * N, bias.shape[1], batch, 1, 0, 0, 1,
+                 splits if epi == PART else 1, batch * M * N, None)
+        for kind, nb in plans:
+            C = torch.full((planes, batch, M, N), float("nan"), dtype=out, device="cuda")
+            d.C = C.data_ptr()
+            rc = f(ctypes.byref(d), ctypes.byref(Plan(kind, nb, d.splits)),
+                   P(torch.cuda.current_stream().cuda_stream or None))
+            assert rc == 0
+            torch.cuda.synchronize()
+            err = float((C.double().sum(0) - ref).norm() / ref.norm())
+            assert err <= tol, (M, N, K, batch, splits, kind, nb, err)
