@@ -205,26 +205,35 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Modelled time (us) of a GEMM of `tiles` workgroups whose reduction is `slices` 128-byte
 // slices long: launch + rounds of workgroups x (prologue and epilogue + slices).  The
-// constants are a fit to measured times (12 to 79 us kernels; fp16 / bf16: 2849 runs over 65
-// to 17228 rows, widths 256 to 16384, 1 to 8 K splits; fp32: 928 runs): the plan with the
+// constants are a fit to measured times (5 to 500 us kernels; fp16 / bf16: 2638 runs over 65
+// to 17228 rows, widths 256 to 16384, 1 to 8 K splits; fp32: 772 runs): the plan with the
 // least modelled time is on average 3% (fp32 2%) slower than the fastest of all plans.
 struct TileCost {
   double launch, round, slice, slice_half, slice_nb;
 };
-constexpr TileCost COST16_256{0.0, 7.9, 1.24, 0, 0}, COST16_128{2.2, 1.2, 1.08, 0.71, 0},
-    COST16_MID{3.2, 1.5, 0.16, 0, 0.12};
-constexpr TileCost COST32_256{3.5, 7.1, 7.1, 0, 0}, COST32_128{4.1, 0.1, 3.76, 1.99, 0},
-    COST32_MID{3.3, 1.2, 0.15, 0, 0.49};
+constexpr TileCost COST16_256{0.0, 7.6, 1.28, 0, 0}, COST16_128{1.7, 1.3, 1.13, 0.72, 0},
+    COST16_MID{2.4, 1.25, 0.17, 0, 0.106};
+constexpr TileCost COST32_256{3.7, 6.9, 7.07, 0, 0}, COST32_128{4.1, 0.1, 3.74, 1.98, 0},
+    COST32_MID{2.8, 1.4, 0.105, 0, 0.466};
+// The GELU epilogue per round of 256 x 256 and 128 x 128 tiles (768 -> 3072 columns, 4 x 2048
+// rows: 384 tiles of 256 x 256 65 us, 1536 of 128 x 128 55 us).
+constexpr double GELU_256 = 5.0, GELU_128 = 1.2;
+// The streaming kernel is considered up to this many rows of activations, and beyond them only
+// where 128 x 128 tiles would leave CUs without a workgroup: it reads its A tile from LDS once
+// per 32 MFMAs of a wave, and with more rows and enough tiles was never the fastest measured
+// 16-bit plan (512 rows: 27 us against 32 us for 2048 -> 8192 columns; 2048 rows, 768 -> 768
+// columns of four sub-layers, 384 tiles: 25 us against 18 us).
+constexpr int MID_MAX_ROWS = 512;
 
-double cost_256(const TileCost& c, int64_t tiles, int64_t slices) {
-  return c.launch + (double)ceil_div(tiles, 256) * (c.round + (double)slices * c.slice);
+double cost_256(const TileCost& c, int64_t tiles, int64_t slices, double epi) {
+  return c.launch + (double)ceil_div(tiles, 256) * (c.round + epi + (double)slices * c.slice);
 }
 // two workgroups per CU; a last round that leaves every CU at most one of them runs its
 // slices faster (slice_half)
-double cost_128(const TileCost& c, int64_t tiles, int64_t slices) {
+double cost_128(const TileCost& c, int64_t tiles, int64_t slices, double epi) {
   const int64_t full = tiles / 512, rem = tiles % 512;
-  double t = c.launch + (double)full * (c.round + (double)slices * c.slice);
-  if (rem > 0) t += c.round + (double)slices * (rem > 256 ? c.slice : c.slice_half);
+  double t = c.launch + (double)full * (c.round + epi + (double)slices * c.slice);
+  if (rem > 0) t += c.round + epi + (double)slices * (rem > 256 ? c.slice : c.slice_half);
   return t;
 }
 double cost_mid(const TileCost& c, int64_t tiles, int64_t slices, int nb) {
@@ -235,7 +244,7 @@ double cost_mid(const TileCost& c, int64_t tiles, int64_t slices, int nb) {
 }  // namespace
 
 GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
-                   int64_t part_elems) {
+                   int64_t part_elems, bool own_sum) {
   // a few rows of 16-bit operands (a decode step): weight streaming
   if (M <= 64 && epi != EPI_BIAS_M && dt != DType::F32) return {GemmKind::SKINNY, 0, 1};
   const bool f32 = dt == DType::F32;
@@ -252,16 +261,23 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
   };
   const int64_t plane = (int64_t)M * N * batch;
   for (int sp = 1; sp <= 8; ++sp) {
-    // Splits keep at least two slices each; their planes must fit.  A plane costs about
-    // 0.1 us per MB to write and, past the first, 0.2 us per MB for the kernel that sums them.
-    if (sp > 1 && (sp * plane > part_elems || slices < 2 * sp)) break;
+    // Splits keep at least 8 slices each (2 of the four times longer fp32 ones; a shorter
+    // reduction gains under 0.3 us per split); their planes must fit.  A plane costs about
+    // 0.1 us per MB to write and 0.2 us per MB to read in the kernel that sums them, which
+    // without a split would read one as well, unless it is launched for the sum alone (4 us,
+    // and its result and residual pass through it too).
+    if (sp > 1 && (sp * plane > part_elems || slices < (f32 ? 2 : 8) * sp)) break;
     const double mb = (double)plane * 4e-6;
-    const double extra = sp > 1 ? 0.1 * mb * sp + 0.2 * mb * (sp - 1) : 0.0;
+    double extra = 0.0;
+    if (sp > 1) extra = 0.1 * mb * sp + 0.2 * mb * (sp - 1) + (own_sum ? 4.0 + 0.4 * mb : 0.0);
     const int64_t sl = ceil_div(slices, sp);
     consider(GemmKind::TILE256, 0, sp,
-             extra + cost_256(f32 ? COST32_256 : COST16_256, t256 * sp, sl));
+             extra + cost_256(f32 ? COST32_256 : COST16_256, t256 * sp, sl,
+                              epi == EPI_BIAS_N_GELU ? GELU_256 : 0.0));
     consider(GemmKind::TILE128, 0, sp,
-             extra + cost_128(f32 ? COST32_128 : COST16_128, t128 * sp, sl));
+             extra + cost_128(f32 ? COST32_128 : COST16_128, t128 * sp, sl,
+                              epi == EPI_BIAS_N_GELU ? GELU_128 : 0.0));
+    if ((epi == EPI_BIAS_M ? N : M) > MID_MAX_ROWS && t128 * sp >= 256) continue;
     for (int nb = 1; nb <= MID_MAX_NB; ++nb)
       consider(GemmKind::MID, nb, sp,
                extra + cost_mid(f32 ? COST32_MID : COST16_MID,
@@ -298,7 +314,7 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
 
 hipError_t launch_gemm(const GemmDesc& g, hipStream_t s) {
   return launch_gemm_planned(
-      g, plan_gemm(g.dt, g.epi, g.M, g.N, g.K, g.kgroups, g.batch, 0), s);
+      g, plan_gemm(g.dt, g.epi, g.M, g.N, g.K, g.kgroups, g.batch, 0, false), s);
 }
 
 }  // namespace kraken

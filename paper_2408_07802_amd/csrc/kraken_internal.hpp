@@ -108,9 +108,10 @@ struct GemmPlan {
 };
 // Plan of a GEMM of type dt.  part_elems: fp32 elements available for K-split partial planes
 // (0: no split; only EPI_BIAS_N_RES results can be split).
-// Only results that the caller sums itself (see PartSum) may be given part_elems > 0.
+// Only results that the caller sums itself (see PartSum) may be given part_elems > 0; own_sum:
+// the sum takes a launch of its own.
 GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
-                   int64_t part_elems);
+                   int64_t part_elems, bool own_sum);
 hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStream_t s);
 // The kernels of the plans TILE256 / TILE128 and MID (one object file per operand type).
 template <typename S>

@@ -152,13 +152,31 @@ __device__ __forceinline__ void add4(float4& a, float4 b) {
   a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
 }
 
+// p[0] + p[stride] + .. + p[(n - 1) stride] (in that order), four loads in flight at a time: a
+// plain loop waits for each load before the next (measured, four planes of 128 x 4 rows of
+// 1280: 9.8 against 6.3 us).
+__device__ __forceinline__ float4 sum_rows(const float* p, int64_t stride, int n) {
+  auto row = [&](int k) { return *reinterpret_cast<const float4*>(p + k * stride); };
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  int k = 0;
+  for (; k + 4 <= n; k += 4) {
+    const float4 b0 = row(k), b1 = row(k + 1), b2 = row(k + 2), b3 = row(k + 3);
+    add4(a, b0); add4(a, b1); add4(a, b2); add4(a, b3);
+  }
+  if (n & 2) {
+    const float4 b0 = row(k), b1 = row(k + 1);
+    add4(a, b0); add4(a, b1);
+    k += 2;
+  }
+  if (n & 1) add4(a, row(k));
+  return a;
+}
+
 // Four elements of a PartSum: row element `at` = (i T + t) d + c of the planes, element
 // i d + c of the biases, res_at = i * res_stride + t d + c of the residual.
 __device__ __forceinline__ float4 part_sum4(const PartSum& ps, int64_t at, int64_t bias_at,
                                             int64_t res_at) {
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < ps.splits; ++s)
-    add4(a, *reinterpret_cast<const float4*>(ps.part + s * ps.plane + at));
+  float4 a = sum_rows(ps.part + at, ps.plane, ps.splits);
   if (ps.bias) add4(a, *reinterpret_cast<const float4*>(ps.bias + bias_at));
   if (ps.bias2) add4(a, *reinterpret_cast<const float4*>(ps.bias2 + bias_at));
   if (ps.res) add4(a, *reinterpret_cast<const float4*>(ps.res + res_at));
@@ -229,12 +247,7 @@ __global__ __launch_bounds__(NORM_THREADS) void combine_ln2_kernel(
     if (shared) {
       y[u] = *reinterpret_cast<const float4*>(shared + (int64_t)t * d + c);
     } else {
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int k = 0; k < n; ++k) {
-        const float4 b = *reinterpret_cast<const float4*>(x + k * plane + (int64_t)t * d + c);
-        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-      }
-      y[u] = a;
+      y[u] = sum_rows(x + (int64_t)t * d + c, plane, n);
     }
   }
   const int i0 = (int)((int64_t)n * blockIdx.y / gridDim.y);

@@ -538,24 +538,29 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // The parallel layer has no kernel that reads h alone: its two projections are split
   // together and their planes summed as one, or neither is.
   const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
-  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N,
-                              parallel ? m->part_elems / 2 : m->part_elems);
-  GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N,
-                              parallel ? m->part_elems / 2 : m->part_elems);
-  if (parallel && plan_o.splits > 1 && plan_d.splits == 1)
-    plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, 0);
-  const bool part_d = plan_d.splits > 1;
-  const bool part_o = parallel ? part_d : plan_o.splits > 1;
+  const int64_t room = parallel ? m->part_elems / 2 : m->part_elems;
+  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, room, false);
+  GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N, room, false);
+  const GemmPlan plan_o_whole =
+      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, 0, false);
+  // the last layer's x has no LayerNorm behind it
+  const GemmPlan plan_d_last =
+      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N, room, true);
   const int64_t plane = N * Td;
   PartSum xsum;                       // the previous layer's x, if it is still in planes
   // W_concat's 16-bit operand: x = hi + lo, written by the last FFN-down projection itself
   // where it is not split and nobody wants x
   const bool wcat16 = D.arch == KRAKEN_ARCH_KRAKEN && dt != DType::F32;
-  const bool hilo_epi = wcat16 && !part_d && !sub_out;
+  const bool part_last = plan_d_last.splits > 1;
+  const bool hilo_epi = wcat16 && !part_last && !sub_out;
 
   for (int j = 0; j < m->L; ++j) {
     const LayerW& w = m->layers[j];
     const bool last = j + 1 == m->L;
+    const GemmPlan& plan_dj = last ? plan_d_last : plan_d;
+    const bool part_d = plan_dj.splits > 1;
+    const bool part_o = parallel ? part_d : plan_o.splits > 1;
+    const GemmPlan& plan_oj = part_o ? plan_o : plan_o_whole;
     const float* xin = j == 0 ? X32 : m->xbuf;   // sub-layer inputs x_i
     const int64_t xs = j == 0 ? 0 : Td;           // first layer: one shared input
     char* cache_j = kv ? kv->cache + (size_t)j * kv->layer_bytes : nullptr;
@@ -634,11 +639,11 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       if (part_o) {
         g.epi = EPI_PART;
         g.C = m->part;
-        g.splits = plan_o.splits; g.sPlane = plane;
-        hsum.part = m->part; hsum.splits = plan_o.splits; hsum.plane = plane;
+        g.splits = plan_oj.splits; g.sPlane = plane;
+        hsum.part = m->part; hsum.splits = plan_oj.splits; hsum.plane = plane;
         hsum.bias = w.bo; hsum.res = xin; hsum.res_stride = xs; hsum.out = m->hbuf;
       }
-      RUN(KRAKEN_K_GEMM_O, launch_gemm_planned(g, plan_o, s), "output projection");
+      RUN(KRAKEN_K_GEMM_O, launch_gemm_planned(g, plan_oj, s), "output projection");
     }
     // The FFN's LayerNorm: Kraken reads h + y with y the combine (Algorithm 1); the
     // GPT-like layer reads h; the parallel layer's FFN takes the LN1 output still in act.
@@ -674,16 +679,16 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       g.M = T; g.N = (int)dp; g.K = (int)Fp; g.batch = (int)N;
       if (part_d) {
         g.epi = EPI_PART;
-        g.splits = plan_d.splits; g.sPlane = plane;
+        g.splits = plan_dj.splits; g.sPlane = plane;
         if (parallel) {
           // x = xin + O planes + FFN planes + bo + b2
-          g.C = m->part + plan_o.splits * plane;
+          g.C = m->part + plan_oj.splits * plane;
           xsum = hsum;
-          xsum.splits += plan_d.splits;
+          xsum.splits += plan_dj.splits;
           xsum.bias2 = w.b2;
         } else {
           g.C = m->part;
-          xsum.part = m->part; xsum.splits = plan_d.splits; xsum.plane = plane;
+          xsum.part = m->part; xsum.splits = plan_dj.splits; xsum.plane = plane;
           xsum.bias = w.b2; xsum.res = m->hbuf; xsum.res_stride = Td;
         }
         xsum.out = m->xbuf;
@@ -692,7 +697,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
         g.sPlane = N * Td;
         g.ovf = ovf;
       }
-      RUN(KRAKEN_K_GEMM_DOWN, launch_gemm_planned(g, plan_d, s), "FFN down");
+      RUN(KRAKEN_K_GEMM_DOWN, launch_gemm_planned(g, plan_dj, s), "FFN down");
     }
   }
 
@@ -700,13 +705,13 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // parallel stack's x goes straight to hidden_out when nothing else needs it.
   const void* hilo = hilo_epi ? static_cast<const void*>(m->xbuf) : m->g;
   bool out_done = false;
-  if (part_d || (wcat16 && !hilo_epi)) {
-    PartSum ps = xsum;
-    if (!part_d) {
+  if (part_last || (wcat16 && !hilo_epi)) {
+    PartSum ps = part_last ? xsum : PartSum();
+    if (!part_last) {
       ps.res = m->xbuf;
       ps.res_stride = Td;
     }
-    ps.out = !part_d || (wcat16 && !sub_out) ? nullptr : m->xbuf;
+    ps.out = !part_last || (wcat16 && !sub_out) ? nullptr : m->xbuf;
     int64_t ld = dp;
     if (D.arch != KRAKEN_ARCH_KRAKEN && hidden_out && !sub_out && !final_rows && d == dp) {
       ps.out = hidden_out;
@@ -748,7 +753,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     } else {
       g.C = hidden_out; g.ldc = (int)d; g.N = (int)d;
     }
-    const GemmPlan plan = plan_gemm(dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, m->part_elems);
+    const GemmPlan plan = plan_gemm(dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, m->part_elems, true);
     if (plan.splits > 1) {
       PartSum ps;
       ps.part = m->part; ps.splits = plan.splits; ps.plane = (int64_t)T * g.N;

@@ -30,10 +30,10 @@ def _lib():
     return kraken.lib()
 
 
-def plan(dt, epi, M, N, K, kgroups, batch, part):
-    f = getattr(_lib(), "_ZN6kraken9plan_gemmENS_5DTypeEiiiiiil")
-    f.argtypes, f.restype = [I] * 7 + [L], Plan
-    return f(dt, epi, M, N, K, kgroups, batch, part)
+def plan(dt, epi, M, N, K, kgroups, batch, part, own_sum=False):
+    f = getattr(_lib(), "_ZN6kraken9plan_gemmENS_5DTypeEiiiiiilb")
+    f.argtypes, f.restype = [I] * 7 + [L, ctypes.c_bool], Plan
+    return f(dt, epi, M, N, K, kgroups, batch, part, own_sum)
 
 
 def test_plans_stay_within_their_limits():
@@ -44,11 +44,11 @@ def test_plans_stay_within_their_limits():
         N, K = 4 * rng.randint(1, 4096), 64 * rng.randint(1, 256)
         g, b = rng.choice([1, 1, 2, 16]), rng.choice([1, 2, 4, 8])
         part = rng.choice([0, M * N * b, 5 * M * N * b, 1 << 40])
-        p = plan(dt, RES, M, N, K, g, b, part)
+        p = plan(dt, RES, M, N, K, g, b, part, rng.random() < 0.5)
         assert (p.kind == SKINNY) == (M <= 64 and dt != F32)
         assert p.kind != MID or 1 <= p.nb <= 6
         slices = K // (32 if dt == F32 else 64) * g
-        assert 1 <= p.splits <= 8 and (p.splits == 1 or 2 * p.splits <= slices)
+        assert 1 <= p.splits <= 8 and (p.splits == 1 or (2 if dt == F32 else 8) * p.splits <= slices)
         assert p.splits == 1 or p.splits * M * N * b <= part
 
 
