@@ -24,7 +24,7 @@ ARCH = "gfx950"
 # type, in parallel
 SOURCES = [
     *[(f"{src}.hip", f"{src}_{t}", [f"-DKRAKEN_T={t}"])
-      for src in ("gemm_tile", "gemm_mid") for t in ("f16", "bf16", "float")],
+      for src in ("gemm_tile", "gemm_mid", "gemm_skinny") for t in ("f16", "bf16", "float")],
     ("attention.hip", "attention", []), ("gemm.hip", "gemm_dispatch", []),
     ("norm.hip", "norm", []), ("decode.hip", "decode", []), ("runtime.hip", "runtime", []),
 ]

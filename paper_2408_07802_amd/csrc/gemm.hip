@@ -4,203 +4,6 @@
 namespace kraken {
 namespace {
 
-// ----------------------------------------------------------------------------- few rows
-//
-// GEMM for a few rows of A (M <= 64: the tokens of a decode step).  Then every weight
-// element is used at most 64 times and the kernel is bound by streaming B (the weights)
-// from HBM once, so the tiling is chosen for parallelism: a workgroup owns TW blocks of
-// 16 output columns of one batch entry and all M rows, and its 4 waves split the
-// (kgroups x K) reduction into 4 contiguous ranges, merged through LDS at the end.  Each
-// step of 32 k is one v_mfma_f32_16x16x32 per (16-row block of A, column block): lane l
-// supplies B column l % 16 and A row l % 16, k = 8 (l / 16) .. + 7 (one 16-byte load
-// each), and gets D rows 4 (l / 16) .. + 3 of column l % 16.  A rows past M load row
-// M - 1 and are masked to zero (whole 16-byte loads without branches: per-lane
-// conditional loads compile to four 4-byte loads each and halved the throughput at 8
-// rows); B columns past N load a clamped row and are not stored.
-template <typename S>
-__device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
-  if constexpr (__is_same(S, bf16)) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-  } else {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
-                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  }
-}
-
-constexpr int SK_UNROLL = 8;   // steps of 32 k whose loads are issued together
-
-// 16-byte weight load (plain: non-temporal loads measured the same, within 3%, on weight
-// streams that do not fit the last-level cache).
-__device__ __forceinline__ uint4 load_w16(const void* ptr) {
-  return *reinterpret_cast<const uint4*>(ptr);
-}
-
-template <typename S, int MB, int TW, int EPI>
-__global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmParams p) {
-  __shared__ float red[4][MB * TW][256];
-  using OutT = std::conditional_t<epi_f32<EPI>, float, S>;
-  const int z = blockIdx.y;
-  const int n0 = blockIdx.x * 16 * TW;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = lane & 15, kq = lane >> 4;
-  const S* Bz[TW];
-#pragma unroll
-  for (int w = 0; w < TW; ++w)
-    Bz[w] = static_cast<const S*>(p.B) + z * p.sB +
-            (int64_t)min(n0 + w * 16 + col, p.N - 1) * p.ldb + kq * 8;
-  // A rows past M load row M - 1 (whole 16-byte loads, no branches) and are masked to 0
-  const S* Az[MB];
-  uint32_t amask[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int m = mb * 16 + col;
-    amask[mb] = m < p.M ? 0xffffffffu : 0u;
-    Az[mb] = static_cast<const S*>(p.A) + z * p.sA + (int64_t)min(m, p.M - 1) * p.lda + kq * 8;
-  }
-  auto load_a = [&](int mb, int64_t off) {
-    uint4 v = *reinterpret_cast<const uint4*>(Az[mb] + off);
-    v.x &= amask[mb]; v.y &= amask[mb]; v.z &= amask[mb]; v.w &= amask[mb];
-    return v;
-  };
-  const int steps_per_group = p.K / 32;
-  const int steps = steps_per_group * p.kgroups;
-  const int t0 = (int)((int64_t)steps * wave / 4), t1 = (int)((int64_t)steps * (wave + 1) / 4);
-  f32x4 acc[MB * TW];
-#pragma unroll
-  for (int q = 0; q < MB * TW; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // step t covers k = 32 (t mod steps_per_group) .. + 31 of group g = t / steps_per_group;
-  // (g, kk) is tracked incrementally from this wave's first step
-  int g = t0 / steps_per_group, kk = (t0 - g * steps_per_group) * 32;
-  int gb = g % p.gBmod;
-  auto advance = [&]() {
-    kk += 32;
-    if (kk == p.K) {
-      kk = 0;
-      ++g;
-      if (++gb == p.gBmod) gb = 0;
-    }
-  };
-  int t = t0;
-  for (; t + SK_UNROLL <= t1; t += SK_UNROLL) {
-    uint4 bv[SK_UNROLL][TW], av[SK_UNROLL][MB];
-    int64_t ao[SK_UNROLL], bo[SK_UNROLL];
-#pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u) {
-      ao[u] = g * p.gA + kk;
-      bo[u] = gb * p.gB + kk;
-      advance();
-    }
-#pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u)
-#pragma unroll
-      for (int w = 0; w < TW; ++w) bv[u][w] = load_w16(Bz[w] + bo[u]);
-#pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-        av[u][mb] = load_a(mb, ao[u]);
-#pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int w = 0; w < TW; ++w)
-          acc[mb * TW + w] = mfma16<S>(av[u][mb], bv[u][w], acc[mb * TW + w]);
-  }
-  for (; t < t1; ++t) {
-    uint4 bv[TW];
-#pragma unroll
-    for (int w = 0; w < TW; ++w) bv[w] = load_w16(Bz[w] + gb * p.gB + kk);
-    const int64_t ao = g * p.gA + kk;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const uint4 av = load_a(mb, ao);
-#pragma unroll
-      for (int w = 0; w < TW; ++w) acc[mb * TW + w] = mfma16<S>(av, bv[w], acc[mb * TW + w]);
-    }
-    advance();
-  }
-  // D row 4 kq + j, column col of each 16-row block -> red[wave][mb][row * 16 + col]
-#pragma unroll
-  for (int q = 0; q < MB * TW; ++q)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[wave][q][(kq * 4 + j) * 16 + col] = acc[q][j];
-  __syncthreads();
-  const int tid = threadIdx.x;
-  const float* biasz = p.bias ? p.bias + z * p.sBias : nullptr;
-  float amax = 0.f;
-#pragma unroll
-  for (int w = 0; w < TW; ++w) {
-    const int n = n0 + w * 16 + (tid & 15);
-    if (n >= p.N) continue;
-    const float bn = biasz ? biasz[n] : 0.f;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int m = mb * 16 + (tid >> 4);
-      if (m >= p.M) break;
-      const int q = mb * TW + w;
-      float v = (red[0][q][tid] + red[1][q][tid]) + (red[2][q][tid] + red[3][q][tid]) + bn;
-      if constexpr (EPI == EPI_BIAS_N_GELU) v = gelu_erf(v);
-      if constexpr (epi_res<EPI>) {
-        if (p.R) v += p.R[z * p.sR + (int64_t)m * p.ldc + n];
-      }
-      track4<OutT>(amax, make_float4(v, 0.f, 0.f, 0.f));
-      OutT* dst = static_cast<OutT*>(p.C) + z * p.sC + (int64_t)m * p.ldc + n;
-      store_val<OutT>(dst, v);
-      if constexpr (EPI == EPI_BIAS_N_HILO) store_val<OutT>(dst + p.sPlane, v - (float)(S)v);
-    }
-  }
-  flag_overflow<OutT>(amax, p.ovf);
-}
-
-template <typename S, int MB, int TW>
-hipError_t launch_skinny(const GemmDesc& g, hipStream_t s) {
-  GemmParams p = gemm_params(g);
-  p.tiles_n = (g.N + 16 * TW - 1) / (16 * TW);
-  dim3 grid((unsigned)p.tiles_n, (unsigned)g.batch), block(256);
-  switch (g.epi) {
-    case EPI_BIAS_N:
-      hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, EPI_BIAS_N>), grid, block, 0, s, p);
-      break;
-    case EPI_BIAS_N_GELU:
-      hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, EPI_BIAS_N_GELU>), grid, block, 0, s, p);
-      break;
-    case EPI_BIAS_N_RES:
-      hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, EPI_BIAS_N_RES>), grid, block, 0, s, p);
-      break;
-    case EPI_BIAS_N_HILO:
-      hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, EPI_BIAS_N_HILO>), grid, block, 0, s, p);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-// Two 16-column blocks per wave (each A fragment feeds two MFMAs, halving the A loads per
-// weight byte) for several rows and reductions up to 4096; one block (twice the
-// workgroups) otherwise.  Measured on the N=8, d=2048 decode projections with weights
-// streamed from HBM: one row, one block 5-18% faster for every projection (FFN down 54
-// against 66 us); eight rows, two blocks 4-5% faster at K = 2048, one block 5% faster at
-// K = 8192.
-template <typename S, int MB>
-hipError_t launch_skinny_tw(const GemmDesc& g, hipStream_t s) {
-  if (g.M > 1 && (int64_t)g.K * g.kgroups <= 4096) return launch_skinny<S, MB, 2>(g, s);
-  return launch_skinny<S, MB, 1>(g, s);
-}
-
-template <typename S>
-hipError_t launch_skinny_rows(const GemmDesc& g, hipStream_t s) {
-  if (g.M <= 16) return launch_skinny_tw<S, 1>(g, s);
-  if (g.M <= 32) return launch_skinny_tw<S, 2>(g, s);
-  return launch_skinny_tw<S, 4>(g, s);
-}
-
-}  // namespace
-
-namespace {
-
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Modelled time (us) of a GEMM of `tiles` workgroups whose reduction is `slices` 128-byte
@@ -241,22 +44,51 @@ double cost_mid(const TileCost& c, int64_t tiles, int64_t slices, int nb) {
                         (c.round + (double)slices * (c.slice + c.slice_nb * nb));
 }
 
+// A few rows (a decode step): whether the kernel for them is the faster one, and its form.
+// Measured with weights from HBM, fp16 (us; 16 columns x 4 waves per workgroup before):
+//   1 row     2048 -> 4096  7.6 -> 6.8 with 8 waves, 8192 -> 2048 19.9 -> 14.8, eight sub-layers
+//             of 8192 -> 2048 56.0 -> 50.1; 1280 -> 51200 27.9 (8 waves: 34.3)
+//   8 rows    eight of 2048 -> 8192 59.4, with two column blocks per workgroup 57.8; one
+//             2048 -> 2048 6.5, two blocks 8.7
+//   24 rows   2048 -> 2048 8.4, the streaming kernel 10.7; 2048 -> 6144 13.1 and 12.5; eight of
+//             8192 -> 2048 81 and 65; past 32 rows the streaming kernel is the faster one
+//             everywhere (64 rows, eight of 2048 -> 8192: 119 and 80)
+//   fp32      four of 4096 -> 1024 at 1 row 24.1 with 8 waves, 19.0 with 16; at 64 rows 48.5, the
+//             streaming kernel 70
+bool skinny_wins(bool f32, int M, int N, int64_t Kall, int batch, int64_t part_elems) {
+  if (M > 64) return false;
+  if (M <= 16 || f32) return true;
+  // 17 to 32 rows: few columns and a reduction that is short or cannot be split
+  return M <= 32 && (int64_t)N * batch <= 4096 && (Kall <= 2048 || part_elems == 0);
+}
+
+GemmPlan skinny_plan(bool f32, int M, int N, int64_t Kall, int batch) {
+  const int64_t blocks = ceil_div(N, 16) * batch;   // workgroups of one column block
+  GemmPlan p{GemmKind::SKINNY, 1, 1, 4};
+  if (f32 && M <= 16) p.waves = 16;
+  else if (f32 || Kall >= 2048 || blocks <= 512) p.waves = 8;
+  // two column blocks (each A fragment feeds two MFMAs) once they still fill the chip
+  if (!f32 && M > 1 && blocks >= 1024 && Kall >= 2048) p.nb = 2;
+  return p;
+}
+
 }  // namespace
 
 GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
                    int64_t part_elems, bool own_sum) {
-  // a few rows of 16-bit operands (a decode step): weight streaming
-  if (M <= 64 && epi != EPI_BIAS_M && dt != DType::F32) return {GemmKind::SKINNY, 0, 1};
   const bool f32 = dt == DType::F32;
+  const int64_t Kall = (int64_t)K * kgroups;
+  if (epi != EPI_BIAS_M && epi != EPI_PART && skinny_wins(f32, M, N, Kall, batch, part_elems))
+    return skinny_plan(f32, M, N, Kall, batch);
   const int64_t slices = (int64_t)K / (f32 ? 32 : 64) * kgroups;
   const int64_t t256 = ceil_div(M, 256) * ceil_div(N, 256) * batch;
   const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128) * batch;
-  GemmPlan best{GemmKind::TILE256, 0, 1};
+  GemmPlan best{GemmKind::TILE256, 0, 1, 0};
   double best_t = 1e30;
   auto consider = [&](GemmKind kind, int nb, int splits, double t) {
     if (t < best_t) {
       best_t = t;
-      best = {kind, nb, splits};
+      best = {kind, nb, splits, 0};
     }
   };
   const int64_t plane = (int64_t)M * N * batch;
@@ -296,10 +128,15 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
   const int64_t es = (int64_t)dtype_size(g.dt);
   if ((int64_t)g.M * g.lda * es >= (1ll << 31) || (int64_t)g.N * g.ldb * es >= (1ll << 31))
     return hipErrorInvalidValue;
+  if (g.gA2 != 0 && (plan.kind != GemmKind::SKINNY || g.epi != EPI_BIAS_N_RES))
+    return hipErrorInvalidValue;
+  if (plan.kind == GemmKind::SKINNY && (g.M > 64 || g.epi == EPI_BIAS_M || g.epi == EPI_PART))
+    return hipErrorInvalidValue;
   switch (plan.kind) {
     case GemmKind::SKINNY:
-      return g.dt == DType::BF16 ? launch_skinny_rows<bf16>(g, s)
-             : g.dt == DType::F16 ? launch_skinny_rows<f16>(g, s) : hipErrorInvalidValue;
+      return g.dt == DType::BF16 ? launch_gemm_skinny<bf16>(g, plan.nb, plan.waves, s)
+             : g.dt == DType::F16 ? launch_gemm_skinny<f16>(g, plan.nb, plan.waves, s)
+                                  : launch_gemm_skinny<float>(g, plan.nb, plan.waves, s);
     case GemmKind::MID:
       return g.dt == DType::BF16 ? launch_gemm_mid<bf16>(g, plan.nb, s)
              : g.dt == DType::F16 ? launch_gemm_mid<f16>(g, plan.nb, s)

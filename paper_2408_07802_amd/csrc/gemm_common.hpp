@@ -25,6 +25,7 @@ struct GemmParams {
   int xshare;              // XCDs that work through the same tile groups together (1, 2, 4, 8)
   int splits;              // workgroups that share one tile's reduction (EPI_PART: planes)
   int64_t sPlane;          // elements between partial planes (EPI_PART) or from hi to lo
+  int64_t gA2;             // elements from the first to the second term of A (0: one term)
   int* ovf;                // fp16 outputs: overflow flag (NULL: not checked)
 };
 
@@ -40,6 +41,7 @@ inline GemmParams gemm_params(const GemmDesc& g) {
   p.xshare = 1;
   p.splits = g.splits > 0 ? g.splits : 1;
   p.sPlane = g.sPlane;
+  p.gA2 = g.gA2;
   p.ovf = g.ovf;
   return p;
 }

@@ -92,6 +92,9 @@ struct GemmDesc {
   // elements from the high to the low terms
   int splits;
   int64_t sPlane;
+  // SKINNY with EPI_BIAS_N_RES: != 0 adds a second term of A, gA2 elements behind the first,
+  // multiplied by the same B
+  int64_t gA2;
   // fp16 outputs only: set to 1 (vector store) when a finite fp32 result rounds to an
   // fp16 infinity (|v| >= 65520); NULL: no check
   int* ovf;
@@ -103,8 +106,10 @@ hipError_t launch_gemm(const GemmDesc& g, hipStream_t s);
 enum class GemmKind : int { TILE256, TILE128, MID, SKINNY };
 struct GemmPlan {
   GemmKind kind;
-  int nb;       // MID: 32-column blocks per tile
+  int nb;       // MID: 32-column blocks per tile; SKINNY: 16-column blocks per workgroup (1, 2)
   int splits;   // K splits
+  int waves;    // SKINNY: waves that share a workgroup's reduction (4, 8; 16 for fp32
+                // up to 16 rows)
 };
 // Plan of a GEMM of type dt.  part_elems: fp32 elements available for K-split partial planes
 // (0: no split; only EPI_BIAS_N_RES results can be split).
@@ -113,11 +118,16 @@ struct GemmPlan {
 GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
                    int64_t part_elems, bool own_sum);
 hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStream_t s);
-// The kernels of the plans TILE256 / TILE128 and MID (one object file per operand type).
+// The kernels of the plans TILE256 / TILE128, MID and SKINNY (one object file per operand type).
 template <typename S>
 hipError_t launch_gemm_tile(const GemmDesc& g, bool big, hipStream_t s);
 template <typename S>
 hipError_t launch_gemm_mid(const GemmDesc& g, int nb, hipStream_t s);
+template <typename S>
+hipError_t launch_gemm_skinny(const GemmDesc& g, int tw, int nw, hipStream_t s);
+template <> hipError_t launch_gemm_skinny<bf16>(const GemmDesc&, int, int, hipStream_t);
+template <> hipError_t launch_gemm_skinny<f16>(const GemmDesc&, int, int, hipStream_t);
+template <> hipError_t launch_gemm_skinny<float>(const GemmDesc&, int, int, hipStream_t);
 template <> hipError_t launch_gemm_tile<bf16>(const GemmDesc&, bool, hipStream_t);
 template <> hipError_t launch_gemm_tile<f16>(const GemmDesc&, bool, hipStream_t);
 template <> hipError_t launch_gemm_tile<float>(const GemmDesc&, bool, hipStream_t);

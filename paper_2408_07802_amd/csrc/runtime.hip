@@ -539,7 +539,8 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // together and their planes summed as one, or neither is.
   const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
   const int64_t room = parallel ? m->part_elems / 2 : m->part_elems;
-  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, room, false);
+  GemmPlan plan_o = plan_gemm(dt, parallel ? EPI_PART : EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1,
+                              (int)N, room, false);
   GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N, room, false);
   const GemmPlan plan_o_whole =
       plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, 0, false);
@@ -754,6 +755,10 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       g.C = hidden_out; g.ldc = (int)d; g.N = (int)d;
     }
     const GemmPlan plan = plan_gemm(dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, m->part_elems, true);
+    if (plan.kind == GemmKind::SKINNY && wcat16) {
+      g.kgroups = (int)N;              // both terms of a sub-layer against one read of its weights
+      g.gA2 = N * Td;
+    }
     if (plan.splits > 1) {
       PartSum ps;
       ps.part = m->part; ps.splits = plan.splits; ps.plane = (int64_t)T * g.N;

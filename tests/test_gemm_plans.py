@@ -18,11 +18,12 @@ class Desc(ctypes.Structure):       # kraken::GemmDesc
     _fields_ = [("dt", I), ("epi", I), ("A", P), ("B", P), ("C", P), ("bias", P), ("R", P),
                 ("M", I), ("N", I), ("K", I), ("lda", I), ("ldb", I), ("ldc", I), ("sA", L),
                 ("sB", L), ("sC", L), ("sR", L), ("sBias", L), ("batch", I), ("kgroups", I),
-                ("gA", L), ("gB", L), ("gBmod", I), ("splits", I), ("sPlane", L), ("ovf", P)]
+                ("gA", L), ("gB", L), ("gBmod", I), ("splits", I), ("sPlane", L),
+                ("gA2", L), ("ovf", P)]
 
 
 class Plan(ctypes.Structure):       # kraken::GemmPlan
-    _fields_ = [("kind", I), ("nb", I), ("splits", I)]
+    _fields_ = [("kind", I), ("nb", I), ("splits", I), ("waves", I)]
 
 
 def _lib():
@@ -44,8 +45,13 @@ def test_plans_stay_within_their_limits():
         N, K = 4 * rng.randint(1, 4096), 64 * rng.randint(1, 256)
         g, b = rng.choice([1, 1, 2, 16]), rng.choice([1, 2, 4, 8])
         part = rng.choice([0, M * N * b, 5 * M * N * b, 1 << 40])
-        p = plan(dt, RES, M, N, K, g, b, part, rng.random() < 0.5)
-        assert (p.kind == SKINNY) == (M <= 64 and dt != F32)
+        epi = rng.choice([RES, RES, PART])
+        p = plan(dt, epi, M, N, K, g, b, part, rng.random() < 0.5)
+        assert epi != PART or p.kind != SKINNY
+        assert p.kind != SKINNY or M <= 64
+        assert p.kind == SKINNY or epi == PART or M > (64 if dt == F32 else 16)
+        waves = (4, 8, 16) if M <= 16 and dt == F32 else (4, 8)
+        assert p.kind != SKINNY or (p.nb in (1, 2) and p.waves in waves)
         assert p.kind != MID or 1 <= p.nb <= 6
         slices = K // (32 if dt == F32 else 64) * g
         assert 1 <= p.splits <= 8 and (p.splits == 1 or (2 if dt == F32 else 8) * p.splits <= slices)
@@ -100,7 +106,7 @@ def test_every_plan_at_tile_edges(dt, epi):
         planes = splits if epi == PART else 2 if epi == HILO else 1
         d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
                  K, K, N, M * K, N * K, M * N, M * N, bias.shape[1], batch, 1, 0, 0, 1,
-                 splits if epi == PART else 1, batch * M * N, None)
+                 splits if epi == PART else 1, batch * M * N, 0, None)
         for kind, nb in plans:
             C = torch.full((planes, batch, M, N), float("nan"), dtype=out, device="cuda")
             d.C = C.data_ptr()
@@ -110,3 +116,53 @@ def test_every_plan_at_tile_edges(dt, epi):
             torch.cuda.synchronize()
             err = float((C.double().sum(0) - ref).norm() / ref.norm())
             assert err <= tol, (M, N, K, batch, splits, kind, nb, err)
+
+
+# a few rows: one to four blocks of 16, column counts that are no multiple of 16 or 32, steps of
+# the reduction that do not divide over the waves (some waves have none)
+FEW_ROWS = [(1, 300, 64, 2), (5, 1000, 2048, 3), (16, 64, 8192, 1), (17, 33, 320, 2),
+            (33, 520, 2112, 2), (64, 130, 704, 2)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dual", [False, True])
+@pytest.mark.parametrize("epi", [BIAS_N, GELU, RES, HILO])
+@pytest.mark.parametrize("dt", [F32, BF16, F16])
+def test_every_few_row_plan(dt, epi, dual):
+    if dt == F32 and (epi == HILO or dual) or dual and epi != RES:
+        pytest.skip("not a kernel")
+    f = getattr(_lib(), "_ZN6kraken19launch_gemm_plannedERKNS_8GemmDescERKNS_8GemmPlanEP12ihipStream_t")
+    f.restype = I
+    S = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[dt]
+    out = torch.float32 if epi == RES else S
+    # as above
+    tol = {torch.float32: 1e-5, torch.float16: 4e-4, torch.bfloat16: 3.2e-3}[out]
+    if epi == HILO:
+        tol = {BF16: 2e-5, F16: 1e-6}[dt]
+    for M, N, K, batch in FEW_ROWS:
+        g = torch.Generator(device="cuda").manual_seed(M + N + K)
+        # two terms of A: the second one is the kernel's only where it reads two
+        A = torch.randn((2, batch, M, K), generator=g, device="cuda").to(S)
+        B = (torch.randn((batch, N, K), generator=g, device="cuda") / math.sqrt(K)).to(S)
+        bias = torch.randn((batch, N), generator=g, device="cuda")
+        R = torch.randn((batch, M, N), generator=g, device="cuda")
+        a64 = A.double().sum(0) if dual else A[0].double()
+        ref = torch.stack([a @ b.T for a, b in zip(a64, B.double())]) + bias.double()[:, None]
+        if epi == GELU:
+            ref = torch.nn.functional.gelu(ref)
+        if epi in (RES, HILO):
+            ref = ref + R.double()
+        d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
+                 K, K, N, M * K, N * K, M * N, M * N, N, batch, 1, 0, 0, 1, 1, batch * M * N,
+                 batch * M * K if dual else 0, None)
+        for tw in (1, 2):
+            for waves in (4, 8, 16) if M <= 16 and dt == F32 else (4, 8):
+                C = torch.full((2 if epi == HILO else 1, batch, M, N), float("nan"), dtype=out,
+                               device="cuda")
+                d.C = C.data_ptr()
+                rc = f(ctypes.byref(d), ctypes.byref(Plan(SKINNY, tw, 1, waves)),
+                       P(torch.cuda.current_stream().cuda_stream or None))
+                assert rc == 0
+                torch.cuda.synchronize()
+                err = float((C.double().sum(0) - ref).norm() / ref.norm())
+                assert err <= tol, (M, N, K, batch, tw, waves, err)
