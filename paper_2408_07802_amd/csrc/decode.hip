@@ -140,6 +140,7 @@ struct DecAttnParams {
   const void* qk;   // [n][B][d + dkv], Q at columns 0..d-1
   const void* cache;
   float* part;      // [n][B][H][S][hd + 2]: max, sum, unnormalised output
+  void* out;        // [n][B][d]: written here if one chunk covers every key (S = 1)
   int n, B, d, dkv, H, Hkv, group, max_seqs, cap, S, chunk;
   float scale;      // 1 / sqrt(hd); ln 2 when Q already carries log2(e) / sqrt(hd)
   int lens[KRAKEN_MAX_SEQS];   // cached tokens of slot b, new token included at lens[b]
@@ -328,12 +329,20 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(DecAttnParams p) {
     float sw[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) sw[w] = M == -INFINITY ? 0.f : __expf(wm[w][g] - M);
-    for (int f = tid; f < HD; f += 256)
-      out[2 + f] = (wo[0][g][f] * sw[0] + wo[1][g][f] * sw[1]) +
-                   (wo[2][g][f] * sw[2] + wo[3][g][f] * sw[3]);
-    if (tid == 0) {
+    const float L = (wl[0][g] * sw[0] + wl[1][g] * sw[1]) + (wl[2][g] * sw[2] + wl[3][g] * sw[3]);
+    for (int f = tid; f < HD; f += 256) {
+      const float o = (wo[0][g][f] * sw[0] + wo[1][g][f] * sw[1]) +
+                      (wo[2][g][f] * sw[2] + wo[3][g][f] * sw[3]);
+      // one chunk: its partial is the result (the merge would scale it by e^0 = 1); without
+      // the merge launch, 128 sequences of up to 937 keys take 6 us less
+      if (p.S == 1)
+        static_cast<S*>(p.out)[((int64_t)i * p.B + b) * p.d + (h0 + g) * HD + f] = (S)(o / L);
+      else
+        out[2 + f] = o;
+    }
+    if (tid == 0 && p.S > 1) {
       out[0] = M;
-      out[1] = (wl[0][g] * sw[0] + wl[1][g] * sw[1]) + (wl[2][g] * sw[2] + wl[3][g] * sw[3]);
+      out[1] = L;
     }
   }
 }
@@ -472,7 +481,7 @@ hipError_t launch_decode_attention(DType dt, const void* qk, const void* cache_l
   int chunk = (int)std::min<int64_t>(std::max<int64_t>(want, DEC_KEYS), 6 * DEC_KEYS);
   while ((max_keys + chunk - 1) / chunk > max_splits) chunk += DEC_KEYS;
   DecAttnParams p;
-  p.qk = qk; p.cache = cache_layer; p.part = part;
+  p.qk = qk; p.cache = cache_layer; p.part = part; p.out = out;
   p.n = n; p.B = B; p.d = d; p.dkv = kvh * hd; p.H = n_heads; p.Hkv = kvh; p.group = group;
   p.max_seqs = max_seqs; p.cap = capacity;
   p.chunk = chunk;
@@ -486,7 +495,7 @@ hipError_t launch_decode_attention(DType dt, const void* qk, const void* cache_l
     case DType::F16: e = decode_attn_typed<f16>(p, hd, qg, s); break;
     default: e = decode_attn_typed<float>(p, hd, qg, s); break;
   }
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || p.S == 1) return e;
   DecCombineParams c;
   c.part = part; c.out = out; c.n = n; c.B = B; c.d = d; c.H = n_heads; c.hd = hd; c.S = p.S;
   dim3 grid((unsigned)((int64_t)n * B * n_heads));

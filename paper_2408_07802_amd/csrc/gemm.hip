@@ -20,13 +20,13 @@ constexpr TileCost COST32_256{3.7, 6.9, 7.07, 0, 0}, COST32_128{4.1, 0.1, 3.74, 
     COST32_MID{2.8, 1.4, 0.105, 0, 0.466};
 // The GELU epilogue per round of 256 x 256 and 128 x 128 tiles (768 -> 3072 columns, 4 x 2048
 // rows: 384 tiles of 256 x 256 65 us, 1536 of 128 x 128 55 us).
-constexpr double GELU_256 = 5.0, GELU_128 = 1.2;
-// The streaming kernel is considered up to this many rows of activations, and beyond them only
-// where 128 x 128 tiles would leave CUs without a workgroup: it reads its A tile from LDS once
-// per 32 MFMAs of a wave, and with more rows and enough tiles was never the fastest measured
-// 16-bit plan (512 rows: 27 us against 32 us for 2048 -> 8192 columns; 2048 rows, 768 -> 768
-// columns of four sub-layers, 384 tiles: 25 us against 18 us).
-constexpr int MID_MAX_ROWS = 512;
+constexpr double GELU_256 = 7.0, GELU_128 = 1.2;
+// The streaming kernel is considered up to MID_ROWS rows of activations, and up to
+// MID_ROWS_NARROW where 128 x 128 tiles would leave CUs without a workgroup: it reads its A tile
+// from LDS once per 32 MFMAs of a wave, and beyond that was never clearly the fastest measured
+// 16-bit plan (512 rows, 2048 -> 8192 columns: 27 us, tiles 32; 1500 rows, 768 -> 1536: 10.3 and
+// 11.8; 3000 rows: 16.1 and 13.9; four sub-layers of 2048 rows, 768 -> 768, 384 tiles: 25 and 18).
+constexpr int MID_ROWS = 512, MID_ROWS_NARROW = 1536;
 
 double cost_256(const TileCost& c, int64_t tiles, int64_t slices, double epi) {
   return c.launch + (double)ceil_div(tiles, 256) * (c.round + epi + (double)slices * c.slice);
@@ -92,6 +92,7 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
     }
   };
   const int64_t plane = (int64_t)M * N * batch;
+  const int rows = epi == EPI_BIAS_M ? N : M;
   for (int sp = 1; sp <= 8; ++sp) {
     // Splits keep at least 8 slices each (2 of the four times longer fp32 ones; a shorter
     // reduction gains under 0.3 us per split); their planes must fit.  A plane costs about
@@ -109,7 +110,7 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
     consider(GemmKind::TILE128, 0, sp,
              extra + cost_128(f32 ? COST32_128 : COST16_128, t128 * sp, sl,
                               epi == EPI_BIAS_N_GELU ? GELU_128 : 0.0));
-    if ((epi == EPI_BIAS_M ? N : M) > MID_MAX_ROWS && t128 * sp >= 256) continue;
+    if (rows > (t128 * sp < 256 ? MID_ROWS_NARROW : MID_ROWS)) continue;
     for (int nb = 1; nb <= MID_MAX_NB; ++nb)
       consider(GemmKind::MID, nb, sp,
                extra + cost_mid(f32 ? COST32_MID : COST16_MID,
@@ -131,6 +132,10 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
   if (g.gA2 != 0 && (plan.kind != GemmKind::SKINNY || g.epi != EPI_BIAS_N_RES))
     return hipErrorInvalidValue;
   if (plan.kind == GemmKind::SKINNY && (g.M > 64 || g.epi == EPI_BIAS_M || g.epi == EPI_PART))
+    return hipErrorInvalidValue;
+  if (g.epi == EPI_QKV &&
+      (!g.qkv || (plan.kind != GemmKind::SKINNY && plan.kind != GemmKind::MID) ||
+       (g.qkv->cache && g.M > 256)))
     return hipErrorInvalidValue;
   switch (plan.kind) {
     case GemmKind::SKINNY:

@@ -163,6 +163,25 @@ __device__ __forceinline__ float4 split_lo(float4 v) {
                      v.w - (float)(S)v.w);
 }
 
+// The QkvOut kernel argument of EPI_QKV kernels (nothing for the others).
+struct NoQkv {};
+template <int EPI>
+using QkvArg = std::conditional_t<EPI == EPI_QKV, QkvOut, NoQkv>;
+template <int EPI>
+QkvArg<EPI> qkv_arg(const GemmDesc& g) {
+  if constexpr (EPI == EPI_QKV) return *g.qkv;
+  else return {};
+}
+
+// Element of the layer's KV cache that column c >= 0 of K | V (batch entry z, row m) goes to.
+__device__ __forceinline__ int64_t kv_place(const QkvOut& o, int z, int m, int c) {
+  const int kv = c >= o.dkv ? 1 : 0;
+  c -= kv * o.dkv;
+  const int h = c / o.hd, e = c - h * o.hd;
+  return (((((int64_t)z * 2 + kv) * o.max_seqs + m) * o.Hkv + h) * (int64_t)o.cap + o.lens[m]) *
+             o.hd + e;
+}
+
 constexpr int MID_BM = 128;    // rows of a gemm_mid_kernel tile
 constexpr int MID_MAX_NB = 6;  // its widest tile: 6 blocks of 32 columns
 

@@ -83,7 +83,7 @@ __device__ __forceinline__ void mid_load(uint32_t dst, uint32_t stage_bytes, con
 }
 
 template <typename S, int NB, int EPI>
-__global__ __launch_bounds__(512, 1) void gemm_mid_kernel(GemmParams p) {
+__global__ __launch_bounds__(512, 1) void gemm_mid_kernel(GemmParams p, QkvArg<EPI> kv) {
   constexpr int BM = MID_BM, BN = 32 * NB;
   constexpr int CH = 8;                        // 16-byte chunks per 128-byte row
   constexpr int EPC = 16 / sizeof(S);
@@ -269,6 +269,14 @@ __global__ __launch_bounds__(512, 1) void gemm_mid_kernel(GemmParams p) {
       v.x += bm; v.y += bm; v.z += bm; v.w += bm;
     }
     const int64_t at = (int64_t)m * p.ldc + n;
+    if constexpr (EPI == EPI_QKV) {            // (segments of 4 columns stay in one head)
+      if (kv.cache && n >= kv.dq) {
+        track4<OutT>(amax, v);
+        store4<S>(static_cast<S*>(kv.cache) + kv_place(kv, z, m, n - kv.dq), v);
+        continue;
+      }
+      if (!kv.cache && n >= kv.dq + kv.dkv) continue;      // V^T: below
+    }
     if (vec_ok && n + 3 < p.N) {
       if (Rz) {
         const float4 rr = *reinterpret_cast<const float4*>(Rz + at);
@@ -291,6 +299,33 @@ __global__ __launch_bounds__(512, 1) void gemm_mid_kernel(GemmParams p) {
       }
     }
   }
+  if constexpr (EPI == EPI_QKV) {
+    // V transposed: lanes take consecutive features, each eight tokens of one
+    const int dqk = kv.dq + kv.dkv;
+    if (!kv.cache && n0 + BN > dqk) {
+      for (int idx = tid; idx < BN * (BM / 8); idx += 512) {
+        const int f = idx % BN, mg = idx / BN, n = n0 + f, m = m0 + mg * 8;
+        if (n < dqk || n >= p.N || m >= p.M) continue;
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = stage[(mg * 8 + k) * RS + f];
+        S* dst = static_cast<S*>(kv.vt) + z * kv.svt + (int64_t)(n - dqk) * kv.ldv + m;
+        if (m + 8 <= p.M) {
+          track4<OutT>(amax, make_float4(v[0], v[1], v[2], v[3]));
+          track4<OutT>(amax, make_float4(v[4], v[5], v[6], v[7]));
+          store4<S>(dst, make_float4(v[0], v[1], v[2], v[3]));
+          store4<S>(dst + 4, make_float4(v[4], v[5], v[6], v[7]));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            if (m + k >= p.M) break;
+            track4<OutT>(amax, make_float4(v[k], 0.f, 0.f, 0.f));
+            store_val<S>(dst + k, v[k]);
+          }
+        }
+      }
+    }
+  }
   flag_overflow<OutT>(amax, p.ovf);
 }
 
@@ -302,23 +337,33 @@ hipError_t launch_nb(const GemmDesc& g, hipStream_t s) {
   const dim3 grid((unsigned)((int64_t)p.tiles_m * p.tiles_n * p.splits * p.batch)), block(512);
   switch (g.epi) {
     case EPI_BIAS_N:
-      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N>), grid, block, 0, s, p);
+      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N>), grid, block, 0, s, p,
+                         qkv_arg<EPI_BIAS_N>(g));
       break;
     case EPI_BIAS_N_GELU:
-      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N_GELU>), grid, block, 0, s, p);
+      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N_GELU>), grid, block, 0, s, p,
+                         qkv_arg<EPI_BIAS_N_GELU>(g));
       break;
     case EPI_BIAS_N_RES:
-      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N_RES>), grid, block, 0, s, p);
+      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N_RES>), grid, block, 0, s, p,
+                         qkv_arg<EPI_BIAS_N_RES>(g));
       break;
     case EPI_BIAS_M:
-      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_M>), grid, block, 0, s, p);
+      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_M>), grid, block, 0, s, p,
+                         qkv_arg<EPI_BIAS_M>(g));
+      break;
+    case EPI_QKV:
+      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_QKV>), grid, block, 0, s, p,
+                         qkv_arg<EPI_QKV>(g));
       break;
     case EPI_PART:
-      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_PART>), grid, block, 0, s, p);
+      hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_PART>), grid, block, 0, s, p,
+                         qkv_arg<EPI_PART>(g));
       break;
     case EPI_BIAS_N_HILO:
       if constexpr (sizeof(S) == 2) {
-        hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N_HILO>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((gemm_mid_kernel<S, NB, EPI_BIAS_N_HILO>), grid, block, 0, s, p,
+                         qkv_arg<EPI_BIAS_N_HILO>(g));
         break;
       }
       return hipErrorInvalidValue;

@@ -44,7 +44,7 @@ constexpr int SK_UNROLL = 8;   // steps whose loads are issued together
 // DUAL: A holds two terms (the second p.gA2 elements behind the first), both multiplied with
 // the same B fragment: W_concat's hi + lo operand reads its weights once instead of twice.
 template <typename S, int MB, int TW, int NW, int EPI, bool DUAL>
-__global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p) {
+__global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p, QkvArg<EPI> kv) {
   constexpr int EPC = 16 / sizeof(S), KS = 4 * EPC;   // elements per chunk and per step
   constexpr int NA = DUAL ? 2 : 1;
   __shared__ float red[NW][MB * TW][256];
@@ -163,6 +163,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p) {
       if (p.R) v += p.R[z * p.sR + (int64_t)m * p.ldc + n];
     }
     track4<OutT>(amax, make_float4(v, 0.f, 0.f, 0.f));
+    if constexpr (EPI == EPI_QKV) {
+      if (kv.cache && n >= kv.dq) {
+        store_val<S>(static_cast<S*>(kv.cache) + kv_place(kv, z, m, n - kv.dq), v);
+        continue;
+      }
+      if (!kv.cache && n >= kv.dq + kv.dkv) {
+        store_val<S>(static_cast<S*>(kv.vt) + z * kv.svt +
+                         (int64_t)(n - kv.dq - kv.dkv) * kv.ldv + m, v);
+        continue;
+      }
+    }
     OutT* dst = static_cast<OutT*>(p.C) + z * p.sC + (int64_t)m * p.ldc + n;
     store_val<OutT>(dst, v);
     if constexpr (EPI == EPI_BIAS_N_HILO) store_val<OutT>(dst + p.sPlane, v - (float)(S)v);
@@ -178,30 +189,34 @@ hipError_t launch_skinny(const GemmDesc& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_BIAS_N:
       hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_BIAS_N, false>), grid, block, 0,
-                         s, p);
+                         s, p, qkv_arg<EPI_BIAS_N>(g));
       break;
     case EPI_BIAS_N_GELU:
       hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_BIAS_N_GELU, false>), grid, block,
-                         0, s, p);
+                         0, s, p, qkv_arg<EPI_BIAS_N_GELU>(g));
       break;
     case EPI_BIAS_N_RES:
       if constexpr (sizeof(S) == 2) {
         if (g.gA2 != 0) {
           hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_BIAS_N_RES, true>), grid,
-                             block, 0, s, p);
+                             block, 0, s, p, qkv_arg<EPI_BIAS_N_RES>(g));
           break;
         }
       }
       hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_BIAS_N_RES, false>), grid, block,
-                         0, s, p);
+                         0, s, p, qkv_arg<EPI_BIAS_N_RES>(g));
       break;
     case EPI_BIAS_N_HILO:
       if constexpr (sizeof(S) == 2) {
         hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_BIAS_N_HILO, false>), grid,
-                           block, 0, s, p);
+                           block, 0, s, p, qkv_arg<EPI_BIAS_N_HILO>(g));
         break;
       }
       return hipErrorInvalidValue;
+    case EPI_QKV:
+      hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_QKV, false>), grid, block, 0, s, p,
+                         qkv_arg<EPI_QKV>(g));
+      break;
     default:
       return hipErrorInvalidValue;
   }

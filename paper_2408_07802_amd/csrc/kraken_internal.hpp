@@ -67,7 +67,20 @@ enum GemmEpi : int {
   EPI_BIAS_M = 3,       // C (storage type) = acc + bias[m]
   EPI_BIAS_N_HILO = 4,  // v = acc + bias[n] + R[m][n] as two 16-bit terms: C = S(v), and
                         // S(v - S(v)) sPlane elements further
+  EPI_QKV = 6,          // columns Q | K | V of one projection, each to its place (QkvOut)
   EPI_PART = 5          // C (float32)      = acc of one K split, plane sp at C + sp * sPlane
+};
+
+// Where the columns of a merged Q | K | V projection (dq + 2 dkv of them) go.  Decode step
+// (cache != NULL): the Q columns to C (row stride ldc), K and V straight into the layer's KV
+// cache (see launch_kv_store) at position lens[m] of slot m.  Prefill: Q | K to C, V transposed
+// to vt[z][feature][ldv].
+struct QkvOut {
+  void* vt;
+  int64_t svt;              // elements between the batch entries of vt
+  void* cache;
+  int ldv, dq, dkv, hd, Hkv, max_seqs, cap;
+  int lens[256];            // KRAKEN_MAX_SEQS
 };
 
 // C[z][m][n] = epi( sum_g sum_k A[z][g][m][k] * B[z][g mod gBmod][n][k] )
@@ -95,6 +108,7 @@ struct GemmDesc {
   // SKINNY with EPI_BIAS_N_RES: != 0 adds a second term of A, gA2 elements behind the first,
   // multiplied by the same B
   int64_t gA2;
+  const QkvOut* qkv;        // EPI_QKV (host memory, read by the launch)
   // fp16 outputs only: set to 1 (vector store) when a finite fp32 result rounds to an
   // fp16 infinity (|v| >= 65520); NULL: no check
   int* ovf;

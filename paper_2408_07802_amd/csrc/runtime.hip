@@ -69,12 +69,10 @@ kraken_status hip_fail(hipError_t e, const char* what) {
 // Stored layouts (dp, dq, dkv, Fp: the stored widths of Dims below).
 struct LayerW {
   float *ln1_g, *ln1_b, *ln2_g, *ln2_b;  // [N][dp]
-  float *bqk;                            // [N][dq + dkv]
-  float *bv;                             // [N][dkv]
+  float *bqk, *bv;                       // [N][dq + 2 dkv]: Q | K, and V behind them
   float *bo, *b2;                        // [N][dp]
   float *b1;                             // [N][Fp]
-  void *WqkT;                            // [N][dq + dkv][dp]
-  void *WvT;                             // [N][dkv][dp]
+  void *WqkT, *WvT;                      // [N][dq + 2 dkv][dp]: Q | K, and V behind them
   void *WoT;                             // [N][dp][dq]
   void *W1T;                             // [N][Fp][dp]
   void *W2T;                             // [N][dp][Fp]
@@ -342,13 +340,13 @@ size_t carve_weights(kraken_model* m, void* base) {
     w.ln1_b = (float*)c.take(N * dp * 4);
     w.ln2_g = (float*)c.take(N * dp * 4);
     w.ln2_b = (float*)c.take(N * dp * 4);
-    w.bqk = (float*)c.take(N * (dq + dkv) * 4);
-    w.bv = (float*)c.take(N * dkv * 4);
+    w.bqk = (float*)c.take(N * (dq + 2 * dkv) * 4);
+    w.bv = w.bqk + (dq + dkv);
     w.bo = (float*)c.take(N * dp * 4);
     w.b1 = (float*)c.take(N * Fp * 4);
     w.b2 = (float*)c.take(N * dp * 4);
-    w.WqkT = c.take(N * (dq + dkv) * dp * es);
-    w.WvT = c.take(N * dkv * dp * es);
+    w.WqkT = c.take(N * (dq + 2 * dkv) * dp * es);
+    w.WvT = static_cast<char*>(w.WqkT) + (dq + dkv) * dp * es;
     w.WoT = c.take(N * dp * dq * es);
     w.W1T = c.take(N * Fp * dp * es);
     w.W2T = c.take(N * dp * Fp * es);
@@ -413,7 +411,8 @@ hipError_t repack_sub(kraken_model* m, int j, int i, const void* src, hipStream_
   const DType st = m->st, dt = m->dt;
   const size_t es = sz(dt);
   int* of = m->flags;
-  char* WqkT = static_cast<char*>(w.WqkT) + i * (dq + dkv) * dp * es;
+  const int64_t dqkv = dq + 2 * dkv;          // one sub-layer's rows of Q | K | V
+  char* WqkT = static_cast<char*>(w.WqkT) + i * dqkv * dp * es;
   hipError_t e;
 #define R_(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
   R_(launch_to_f32(st, cptr(src, so.ln1_g, st), w.ln1_g + i * dp, d, s));
@@ -423,11 +422,11 @@ hipError_t repack_sub(kraken_model* m, int j, int i, const void* src, hipStream_
     R_(launch_to_f32(st, cptr(src, so.ln2_b, st), w.ln2_b + i * dp, d, s));
   }
   // biases of the Q, K and V columns, each head at a multiple of hdp
-  R_(launch_to_f32_2d(st, cptr(src, so.bqkv, st), 0, w.bqk + i * (dq + dkv), 0, 1, (int)dql, hd,
+  R_(launch_to_f32_2d(st, cptr(src, so.bqkv, st), 0, w.bqk + i * dqkv, 0, 1, (int)dql, hd,
                       hdp, s));
-  R_(launch_to_f32_2d(st, cptr(src, so.bqkv + dql, st), 0, w.bqk + i * (dq + dkv) + dq, 0, 1,
+  R_(launch_to_f32_2d(st, cptr(src, so.bqkv + dql, st), 0, w.bqk + i * dqkv + dq, 0, 1,
                       (int)dkvl, hd, hdp, s));
-  R_(launch_to_f32_2d(st, cptr(src, so.bqkv + dql + dkvl, st), 0, w.bv + i * dkv, 0, 1,
+  R_(launch_to_f32_2d(st, cptr(src, so.bqkv + dql + dkvl, st), 0, w.bv + i * dqkv, 0, 1,
                       (int)dkvl, hd, hdp, s));
   R_(launch_to_f32(st, cptr(src, so.bo, st), w.bo + i * dp, d, s));
   R_(launch_to_f32(st, cptr(src, so.b1, st), w.b1 + i * Fp, F, s));
@@ -444,10 +443,10 @@ hipError_t repack_sub(kraken_model* m, int j, int i, const void* src, hipStream_
   {
     const float qs = (float)(1.4426950408889634 / std::sqrt((double)hd));
     R_(launch_scale(dt, WqkT, dq * dp, qs, s));
-    R_(launch_scale(DType::F32, w.bqk + i * (dq + dkv), dq, qs, s));
+    R_(launch_scale(DType::F32, w.bqk + i * dqkv, dq, qs, s));
   }
   R_(launch_transpose(st, cptr(src, so.Wqkv + dql + dkvl, st), wq, dt,
-                      static_cast<char*>(w.WvT) + i * dkv * dp * es, dp, (int)d, (int)dkvl, of,
+                      static_cast<char*>(w.WvT) + i * dqkv * dp * es, dp, (int)d, (int)dkvl, of,
                       s, 1, 1, hd, hdp));
   R_(launch_transpose(st, cptr(src, so.Wo, st), d, dt, static_cast<char*>(w.WoT) + i * dp * dq * es,
                       dq, (int)dql, (int)d, of, s, hd, hdp, 1, 1));
@@ -528,7 +527,8 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
 
   // Attention reads V^T in 16-byte chunks of 8 tokens; the padding columns [T, ldv) are
   // only ever multiplied by zero probabilities but must hold finite values.
-  const int64_t dq = D.dq, dkv = D.dkv, dqk = dq + dkv;   // stored Q, K/V and Q|K widths
+  const int64_t dq = D.dq, dkv = D.dkv;            // stored Q and K/V widths
+  const int64_t dqk = dq + dkv, dqkv = dqk + dkv;  // of Q | K and of Q | K | V
   if (!decode && ldv > T)
     RUN(KRAKEN_K_OTHER, launch_zero_cols(dt, m->vt, N * dkv, ldv, T, ldv, s), "V padding");
 
@@ -555,6 +555,20 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   const bool part_last = plan_d_last.splits > 1;
   const bool hilo_epi = wcat16 && !part_last && !sub_out;
 
+  // Q, K and V in one projection, each column stored where it is read (Q | K rows and V^T, or a
+  // decode step's cache), where the kernels for few or some hundred rows run it; the tiled
+  // kernels of larger prompts take two projections.  (32-bit offsets: all three together may
+  // be too large for one.)
+  const GemmPlan plan_qkv = plan_gemm(dt, EPI_QKV, T, (int)dqkv, (int)dp, 1, (int)N, 0, false);
+  const bool merged = (plan_qkv.kind == GemmKind::SKINNY || plan_qkv.kind == GemmKind::MID) &&
+                      dqkv * dp * (int64_t)sz(dt) < (1ll << 31);
+  QkvOut qkv = {};
+  qkv.vt = m->vt; qkv.svt = dkv * ldv; qkv.ldv = ldv;
+  qkv.dq = (int)dq; qkv.dkv = (int)dkv; qkv.hd = D.hdp; qkv.Hkv = D.Hkv;
+  qkv.max_seqs = kv ? kv->max_seqs : 0; qkv.cap = kv ? kv->cap : 0;
+  if (decode)
+    for (int b = 0; b < T; ++b) qkv.lens[b] = kv->lens[b];
+
   for (int j = 0; j < m->L; ++j) {
     const LayerW& w = m->layers[j];
     const bool last = j + 1 == m->L;
@@ -572,23 +586,26 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     PartSum hsum;
     {
       GemmDesc g = gemm_base(dt);
-      g.epi = EPI_BIAS_N;
+      g.epi = merged ? EPI_QKV : EPI_BIAS_N;
       g.A = m->act; g.lda = (int)dp; g.sA = Td;
-      g.B = w.WqkT; g.ldb = (int)dp; g.sB = dqk * dp;
+      g.B = w.WqkT; g.ldb = (int)dp; g.sB = dqkv * dp;
       g.C = m->qk; g.ldc = (int)dqk; g.sC = (int64_t)T * dqk;
-      g.bias = w.bqk; g.sBias = dqk;
-      g.M = T; g.N = (int)dqk; g.K = (int)dp; g.batch = (int)N;
+      g.bias = w.bqk; g.sBias = dqkv;
+      g.M = T; g.N = (int)(merged ? dqkv : dqk); g.K = (int)dp; g.batch = (int)N;
       g.ovf = ovf;
-      RUN(KRAKEN_K_GEMM_QK, launch_gemm(g, s), "QK projection");
+      qkv.cache = decode ? cache_j : nullptr;
+      g.qkv = &qkv;
+      RUN(KRAKEN_K_GEMM_QK, merged ? launch_gemm_planned(g, plan_qkv, s) : launch_gemm(g, s),
+          "QK projection");
     }
     if (!decode) {
-      {
+      if (!merged) {
         GemmDesc g = gemm_base(dt);
         g.epi = EPI_BIAS_M;
-        g.A = w.WvT; g.lda = (int)dp; g.sA = dkv * dp;
+        g.A = w.WvT; g.lda = (int)dp; g.sA = dqkv * dp;
         g.B = m->act; g.ldb = (int)dp; g.sB = Td;
         g.C = m->vt; g.ldc = ldv; g.sC = dkv * ldv;
-        g.bias = w.bv; g.sBias = dkv;
+        g.bias = w.bv; g.sBias = dqkv;
         g.M = (int)dkv; g.N = T; g.K = (int)dp; g.batch = (int)N;
         g.ovf = ovf;
         RUN(KRAKEN_K_GEMM_VT, launch_gemm(g, s), "V projection");
@@ -605,23 +622,25 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       a.q_prescaled = 1;
       RUN(KRAKEN_K_ATTN, launch_attention(a, s), "attention");
     } else {
-      // V rows of the new tokens go through o ([N][T][dkv]) into the cache; o then takes
-      // the attention output, after the append has read it (stream order).
-      {
-        GemmDesc g = gemm_base(dt);
-        g.epi = EPI_BIAS_N;
-        g.A = m->act; g.lda = (int)dp; g.sA = Td;
-        g.B = w.WvT; g.ldb = (int)dp; g.sB = dkv * dp;
-        g.C = m->o; g.ldc = (int)dkv; g.sC = (int64_t)T * dkv;
-        g.bias = w.bv; g.sBias = dkv;
-        g.M = T; g.N = (int)dkv; g.K = (int)dp; g.batch = (int)N;
-        g.ovf = ovf;
-        RUN(KRAKEN_K_GEMM_VT, launch_gemm(g, s), "V projection");
+      if (!merged) {
+        // V rows of the new tokens go through o ([N][T][dkv]) into the cache; o then takes
+        // the attention output, after the append has read it (stream order).
+        {
+          GemmDesc g = gemm_base(dt);
+          g.epi = EPI_BIAS_N;
+          g.A = m->act; g.lda = (int)dp; g.sA = Td;
+          g.B = w.WvT; g.ldb = (int)dp; g.sB = dqkv * dp;
+          g.C = m->o; g.ldc = (int)dkv; g.sC = (int64_t)T * dkv;
+          g.bias = w.bv; g.sBias = dqkv;
+          g.M = T; g.N = (int)dkv; g.K = (int)dp; g.batch = (int)N;
+          g.ovf = ovf;
+          RUN(KRAKEN_K_GEMM_VT, launch_gemm(g, s), "V projection");
+        }
+        RUN(KRAKEN_K_KV,
+            launch_kv_append(dt, m->qk, m->o, cache_j, (int)N, T, (int)dq, D.H, D.Hkv, kv->lens,
+                             kv->max_seqs, kv->cap, s),
+            "KV append");
       }
-      RUN(KRAKEN_K_KV,
-          launch_kv_append(dt, m->qk, m->o, cache_j, (int)N, T, (int)dq, D.H, D.Hkv, kv->lens,
-                           kv->max_seqs, kv->cap, s),
-          "KV append");
       RUN(KRAKEN_K_ATTN,
           launch_decode_attention(dt, m->qk, cache_j, static_cast<float*>(m->vt),
                                   decode_partial_room(m), m->o, (int)N, T, (int)dq, D.H, D.Hkv,

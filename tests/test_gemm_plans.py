@@ -19,7 +19,7 @@ class Desc(ctypes.Structure):       # kraken::GemmDesc
                 ("M", I), ("N", I), ("K", I), ("lda", I), ("ldb", I), ("ldc", I), ("sA", L),
                 ("sB", L), ("sC", L), ("sR", L), ("sBias", L), ("batch", I), ("kgroups", I),
                 ("gA", L), ("gB", L), ("gBmod", I), ("splits", I), ("sPlane", L),
-                ("gA2", L), ("ovf", P)]
+                ("gA2", L), ("qkv", P), ("ovf", P)]
 
 
 class Plan(ctypes.Structure):       # kraken::GemmPlan
@@ -106,7 +106,7 @@ def test_every_plan_at_tile_edges(dt, epi):
         planes = splits if epi == PART else 2 if epi == HILO else 1
         d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
                  K, K, N, M * K, N * K, M * N, M * N, bias.shape[1], batch, 1, 0, 0, 1,
-                 splits if epi == PART else 1, batch * M * N, 0, None)
+                 splits if epi == PART else 1, batch * M * N, 0, None, None)
         for kind, nb in plans:
             C = torch.full((planes, batch, M, N), float("nan"), dtype=out, device="cuda")
             d.C = C.data_ptr()
@@ -154,7 +154,7 @@ def test_every_few_row_plan(dt, epi, dual):
             ref = ref + R.double()
         d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
                  K, K, N, M * K, N * K, M * N, M * N, N, batch, 1, 0, 0, 1, 1, batch * M * N,
-                 batch * M * K if dual else 0, None)
+                 batch * M * K if dual else 0, None, None)
         for tw in (1, 2):
             for waves in (4, 8, 16) if M <= 16 and dt == F32 else (4, 8):
                 C = torch.full((2 if epi == HILO else 1, batch, M, N), float("nan"), dtype=out,
