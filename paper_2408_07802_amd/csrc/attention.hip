@@ -181,10 +181,42 @@ __device__ __forceinline__ void wait_vmcnt() {
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// Sum of the eight 16-bit values packed in v, added to acc in fp32 (v_dot2 with (1, 1)).
+template <typename S>
+__device__ __forceinline__ float sum8(uint4 v, float acc);
+template <>
+__device__ __forceinline__ float sum8<f16>(uint4 v, float acc) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
+  acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.x), one, acc, false);
+  acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.y), one, acc, false);
+  acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.z), one, acc, false);
+  return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.w), one, acc, false);
+}
+template <>
+__device__ __forceinline__ float sum8<bf16>(uint4 v, float acc) {
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  const b2 one = {(__bf16)1.0f, (__bf16)1.0f};
+  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.x), one, acc, false);
+  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.y), one, acc, false);
+  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.z), one, acc, false);
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.w), one, acc, false);
+}
+
 // NQB 32-query blocks per wave: NQB = 1 runs 8 waves (two per SIMD, so one wave's
 // softmax arithmetic overlaps the other's matrix work); NQB = 2 runs 4 waves.
-template <typename S, int HD, int NQB>
-__global__ __launch_bounds__(BQ / NQB / 32 * 64, 1) void attn_kernel(AttnParams p) {
+//
+// PRE (16-bit operands whose Q already carries log2(e) / sqrt(hd)): the softmax of the
+// ping-pong form below, i.e. scores accumulate onto -c0 so that a weight is a bare exp2, row
+// sums add the packed weights, and the row maximum is computed only on tiles that can need a
+// new exponent base.  These kernels are bound by their VALU work (heads of 64: 32 exponentials
+// a tile against 16 MFMAs).  Measured, fp16: 17228 tokens in 8 sequences, 4 x 20 heads of 64
+// 666-760 -> 620 us; 4096 tokens, 16 heads of 64 over 4 81 -> 76 us; 1500 tokens, 8 x 32 heads of
+// 32 98 -> 92 us.  (The launch bound keeps heads of 64 at two workgroups per CU; with -c0 kept in
+// 16 registers as in the ping-pong form that costs 80 bytes of spills per lane, 892 us.)
+template <typename S, int HD, int NQB, bool PRE>
+__global__ __launch_bounds__(BQ / NQB / 32 * 64, HD == 64 && sizeof(S) == 2 ? 4 : 1)
+void attn_kernel(AttnParams p) {
   constexpr int QW = 32 * NQB;                // queries per wave
   constexpr int NW = BQ / QW;                 // waves per workgroup
   constexpr int ES = sizeof(S);
@@ -285,10 +317,12 @@ __global__ __launch_bounds__(BQ / NQB / 32 * 64, 1) void attn_kernel(AttnParams 
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[qb][ob][r] = 0.f;
   float m_run[NQB], l_run[NQB];
+  float c0[NQB];                              // (PRE) the S accumulators start from -c0
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     m_run[qb] = -1e30f;
     l_run[qb] = 0.f;
+    c0[qb] = 0.f;
   }
 
   const int n_tiles = (q_hi - kv_begin + BKV - 1) / BKV;
@@ -321,7 +355,8 @@ __global__ __launch_bounds__(BQ / NQB / 32 * 64, 1) void attn_kernel(AttnParams 
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[qb][sb][r] = 0.f;
+        for (int r = 0; r < 16; ++r) st[qb][sb][r] = PRE ? -c0[qb] : 0.f;
+    uint4 pb[NQB][2][2];                        // 16-bit P: [key block][half]
     // (k steps outer, key blocks inner: consecutive MFMAs feed independent accumulators)
 #pragma unroll
     for (int kc = 0; kc < NQC; ++kc)
@@ -353,13 +388,60 @@ __global__ __launch_bounds__(BQ / NQB / 32 * 64, 1) void attn_kernel(AttnParams 
             st[qb][sb][r] = (off - lo <= span) ? st[qb][sb][r] : -INFINITY;
           }
       }
-      float mraw = -INFINITY;
+      auto row_max = [&]() {
+        float mraw = -INFINITY;
 #pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
+        for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mraw = fmaxf(mraw, st[qb][sb][r]);
-      float mx = fmaxf(m_run[qb], mraw * p.scale_log2);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+          for (int r = 0; r < 16; ++r) mraw = fmaxf(mraw, st[qb][sb][r]);
+        const float mx = fmaxf(m_run[qb], PRE ? mraw + c0[qb] : mraw * p.scale_log2);
+        return fmaxf(mx, __shfl_xor(mx, 32, 64));
+      };
+      if constexpr (PRE) {
+        typedef S s8 __attribute__((ext_vector_type(8)));
+        float lsum[4];
+        auto weights = [&]() {
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+              s8 v;
+#pragma unroll
+              for (int j = 0; j < 8; ++j)
+                v[j] = (S)__builtin_amdgcn_exp2f(st[qb][sb][8 * hh + j]);
+              pb[qb][sb][hh] = __builtin_bit_cast(uint4, v);
+              lsum[2 * sb + hh] = sum8<S>(pb[qb][sb][hh], 0.f);
+            }
+        };
+        // (attn_pp_kernel's vector phase states why the shortcut decides alike)
+        bool exact = t == 0;
+        if (!exact) {
+          weights();
+          exact = __ballot((lsum[0] + lsum[1]) + (lsum[2] + lsum[3]) >= 256.0f) != 0;
+        }
+        if (exact) {
+          const float mx = row_max();
+          if (__ballot(mx > m_run[qb] + 8.0f)) {
+            const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - mx);
+            l_run[qb] *= alpha;
+#pragma unroll
+            for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) oacc[qb][ob][r] *= alpha;
+            const float shift = mx - c0[qb];
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) st[qb][sb][r] -= shift;
+            c0[qb] = mx;
+            m_run[qb] = mx;
+          }
+          weights();
+        }
+        l_run[qb] += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
+        continue;
+      }
+      const float mx = row_max();
       // The exponent base m_run is only moved when some lane's maximum exceeds it by
       // more than 8 (log2 units): weights stay <= 2^8, exact in the fp32 sums and within
       // the range of the 16-bit P operand, and the O rescale is rare.
@@ -387,18 +469,19 @@ __global__ __launch_bounds__(BQ / NQB / 32 * 64, 1) void attn_kernel(AttnParams 
     // O^T += V^T P^T
     if constexpr (ES == 2) {
       typedef S s8 __attribute__((ext_vector_type(8)));
-      uint4 pb[NQB][2][2];
+      if constexpr (!PRE) {
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb)
+        for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
+          for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            s8 v;
+            for (int hh = 0; hh < 2; ++hh) {
+              s8 v;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (S)st[qb][sb][8 * hh + j];
-            pb[qb][sb][hh] = __builtin_bit_cast(uint4, v);
-          }
+              for (int j = 0; j < 8; ++j) v[j] = (S)st[qb][sb][8 * hh + j];
+              pb[qb][sb][hh] = __builtin_bit_cast(uint4, v);
+            }
+      }
       // (key chunks outer, output blocks inner: independent accumulators back to back)
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
@@ -488,28 +571,6 @@ __device__ __forceinline__ void sfor(F&& f) {
     f(IC<B>{});
     sfor<B + 1, E>(f);
   }
-}
-
-// Sum of the eight 16-bit values packed in v, added to acc in fp32 (v_dot2 with (1, 1)).
-template <typename S>
-__device__ __forceinline__ float sum8(uint4 v, float acc);
-template <>
-__device__ __forceinline__ float sum8<f16>(uint4 v, float acc) {
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
-  acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.x), one, acc, false);
-  acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.y), one, acc, false);
-  acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.z), one, acc, false);
-  return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, v.w), one, acc, false);
-}
-template <>
-__device__ __forceinline__ float sum8<bf16>(uint4 v, float acc) {
-  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  const b2 one = {(__bf16)1.0f, (__bf16)1.0f};
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.x), one, acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.y), one, acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.z), one, acc, false);
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, v.w), one, acc, false);
 }
 
 // PRE: Q already carries log2(e) / sqrt(hd), so the scores come out of the MFMAs in log2
@@ -891,7 +952,14 @@ void launch_hd(const AttnParams& p, dim3 grid, hipStream_t s) {
       return;
     }
   }
-  hipLaunchKernelGGL((attn_kernel<S, HD, NQB>), grid, dim3(BQ / NQB / 32 * 64), 0, s, p);
+  const dim3 block(BQ / NQB / 32 * 64);
+  if constexpr (sizeof(S) == 2) {
+    if (p.q_prescaled) {
+      hipLaunchKernelGGL((attn_kernel<S, HD, NQB, true>), grid, block, 0, s, p);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((attn_kernel<S, HD, NQB, false>), grid, block, 0, s, p);
 }
 
 template <typename S>
