@@ -651,6 +651,14 @@ __global__ __launch_bounds__(512, 1) void attn_pp_kernel(AttnParams p) {
       qf[kc] = (my_q < q_hi) ? *reinterpret_cast<const uint4*>(qrow + (2 * kc + lhalf) * EPC)
                              : make_uint4(0, 0, 0, 0);
   }
+  // Zeros for the last tile's stage while the Q loads are on their way, if nothing else fills it
+  // first: LDS holds whatever the previous workgroup left, a range-checked load need not write
+  // the bytes of its out-of-range lanes, and a zero weight times a stale NaN would not be zero.
+  // (A stage that the ring comes back to holds an earlier tile of the sequence, whose values
+  // every query of this workgroup has multiplied already.)
+  if (n_tiles <= PP_STAGES)
+    for (int k = tid; k < STAGE / 16; k += NW * 64)
+      smem[(n_tiles - 1) * (STAGE / 16) + k] = make_uint4(0, 0, 0, 0);
   __builtin_amdgcn_s_waitcnt(VMCNT0);        // (visible to the compiler: see attn_kernel)
 
   // this wave's share of the DMA of key tile u (K and V^T) into stage u % PP_STAGES, as
@@ -881,11 +889,8 @@ __global__ __launch_bounds__(512, 1) void attn_pp_kernel(AttnParams p) {
     l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
   };
 
-  // ---- prologue.  The ring starts at zero: LDS holds whatever the previous workgroup
-  // left, a range-checked load need not write the bytes of its out-of-range lanes, and a
-  // zero weight times a stale NaN would not be zero.  Then every wave loads its share of
-  // tiles 0 and 1 (later tiles are issued after M(t)); tile 0 complete at barrier 0.
-  for (int k = tid; k < PP_STAGES * STAGE / 16; k += NW * 64) smem[k] = make_uint4(0, 0, 0, 0);
+  // ---- prologue.  Every wave loads its share of tiles 0 and 1 (later tiles are issued after
+  // M(t)); tile 0 complete at barrier 0.
   __syncthreads();
   issue(0);
   issue(1);

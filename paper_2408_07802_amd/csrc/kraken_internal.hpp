@@ -216,6 +216,12 @@ hipError_t launch_finish(DType dt, const PartSum& ps, int n, int T, int d, int64
 hipError_t launch_to_f32_2d(DType st, const void* src, int64_t src_ld, float* dst,
                             int64_t dst_ld, int R, int C, int g, int gp, hipStream_t s);
 
+// dst[r * dst_ld + c] = float(src[r * src_ld + c]) for c < C, 0 for C <= c < dst_ld, r < R, where
+// rows_to_f32_ok: C and the strides multiples of 4, src aligned to four elements.
+bool rows_to_f32_ok(DType st, const void* src, int64_t src_ld, int64_t dst_ld, int C);
+hipError_t launch_rows_to_f32(DType st, const void* src, int64_t src_ld, float* dst, int64_t dst_ld,
+                              int64_t R, int C, hipStream_t s);
+
 // dst[r * dst_ld + c] = Dst(src[r * src_ld + c]) for r < R, c < C; *overflow as for
 // launch_transpose.
 hipError_t launch_convert_2d(DType src_t, const void* src, int64_t src_ld, DType dst_t, void* dst,

