@@ -49,16 +49,16 @@ COPY_PROBE_BYTES = 1 << 30
 TRAFFIC = {
     "attention": {
         "source": "paper_2408_07802_amd/csrc/attention.hip",
-        "source_sha256": "d36a3271213cc855a692f8cbe52ca89e197b506421157266e20b90d46b78bc18",
-        "read_bytes": 3262133080, "write_bytes": 269231327,
+        "source_sha256": "32c3b0875815dbc07b693ff4d38347e7f2acbd0c2c4729cd2b698cbbc0b5728d",
+        "read_bytes": 3283632289, "write_bytes": 269469279,
         "algorithmic_bytes": 4 * 8 * 8192 * 2048 * 2,
         "profile": "profiles/hbm_traffic_n8_l24_d2048_t8192.md",
     },
     # FFN up projection with the GELU epilogue (A: LN2 output, B: W1, C: the activation)
     "gemm_up": {
-        "source": "paper_2408_07802_amd/csrc/gemm.hip",
-        "source_sha256": "e3b5be6adeb3c4bc7aa9a2404ce5950c6ec763f2b666b5b3039215acb20837bb",
-        "read_bytes": 3224425359, "write_bytes": 1074040672,
+        "source": "paper_2408_07802_amd/csrc/gemm_tile.hip",
+        "source_sha256": "f1dc93bcb808f68ffd6bc0aa3c4dbb47aca788a565382196412281b4cd55520d",
+        "read_bytes": 3224337862, "write_bytes": 1074022680,
         "algorithmic_bytes": 2 * (8 * 8192 * 2048 * 2 + 8 * 8192 * 8192) + 8 * 8192 * 4,
         "profile": "profiles/hbm_traffic_n8_l24_d2048_t8192.md",
     },
@@ -66,8 +66,8 @@ TRAFFIC = {
     # kernel plus its chunk merge
     "decode_attention_b1_ctx8192": {
         "source": "paper_2408_07802_amd/csrc/decode.hip",
-        "source_sha256": "df9a080c2d386a595471223a32068cc34f39fdf729f5379a6d1d5b8a6b132629",
-        "read_bytes": 537726597, "write_bytes": 450560,
+        "source_sha256": "a5b9a13de10dd75687f70c923d1abf9d78b9c25dd45c4835a764ca8852d10fcd",
+        "read_bytes": 537723371, "write_bytes": 450560,
         "algorithmic_bytes": 537034752,
         "profile": "profiles/hbm_traffic_decode_n8_l24_d2048_ctx8192.md",
     },

@@ -1,4 +1,6 @@
-// Dispatch of the batched GEMMs (plan_gemm) and the kernel for a few rows.
+// Dispatch of the batched GEMMs (plan_gemm): which kernel, tile and number of K splits.
+#include <algorithm>
+
 #include "gemm_common.hpp"
 
 namespace kraken {
@@ -6,43 +8,46 @@ namespace {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Modelled time (us) of a GEMM of `tiles` workgroups whose reduction is `slices` 128-byte
-// slices long: launch + rounds of workgroups x (prologue and epilogue + slices).  The
-// constants are a fit to measured times (5 to 500 us kernels; fp16 / bf16: 2638 runs over 65
-// to 17228 rows, widths 256 to 16384, 1 to 8 K splits; fp32: 772 runs): the plan with the
-// least modelled time is on average 3% (fp32 2%) slower than the fastest of all plans.
+// Modelled time (us) of a GEMM of `tiles` workgroups, `slots` of them at a time, whose
+// reduction is `slices` 128-byte slices long: launch + rounds x (prologue and epilogue +
+// slices), a slice taking longer the fuller the round is (operand traffic, clock).  The
+// constants are a fit to measured times (fp16 / bf16: 3193 runs over 65 to 17228 rows, widths
+// 256 to 16384, 1 to 8 K splits; fp32: 850 runs): the plan with the least modelled time is on
+// average 1.5% (fp32 2%) slower than the fastest of all plans.
+// A launch takes at least as long as its weights do at the rate the kernel streams them from
+// HBM (128 rows, 4 x 4992 -> 9984 and 4992 columns: 3.5 TB/s in 128 x 128 tiles, 5.0 through
+// the streaming kernel's tiles of 5 blocks of columns, 2.8 to 3.4 through 1 or 2); a little of
+// the modelled time then breaks ties.
 struct TileCost {
-  double launch, round, slice, slice_half, slice_nb;
+  double launch, round, slice, slice_nb, load, gelu, stream;   // stream: TB/s
+  double us(int64_t tiles, int64_t slots, int64_t slices, int nb, bool with_gelu,
+            double weight_mb) const {
+    auto per_round = [&](double full) {
+      return round + (with_gelu ? gelu : 0.0) +
+             (double)slices * (slice + slice_nb * nb) * (1.0 + load * full);
+    };
+    double t = launch + (double)(tiles / slots) * per_round(1.0);
+    if (tiles % slots) t += per_round((double)(tiles % slots) / (double)slots);
+    const double rate = nb > 0 ? std::min(2.2 + 0.6 * nb, stream) : stream;
+    const double floor = launch + weight_mb / rate;
+    return t > floor ? t : floor + 0.03 * t;
+  }
 };
-constexpr TileCost COST16_256{0.0, 7.6, 1.28, 0, 0}, COST16_128{1.7, 1.3, 1.13, 0.72, 0},
-    COST16_MID{2.4, 1.25, 0.17, 0, 0.106};
-constexpr TileCost COST32_256{3.7, 6.9, 7.07, 0, 0}, COST32_128{4.1, 0.1, 3.74, 1.98, 0},
-    COST32_MID{2.8, 1.4, 0.105, 0, 0.466};
-// The GELU epilogue per round of 256 x 256 and 128 x 128 tiles (768 -> 3072 columns, 4 x 2048
-// rows: 384 tiles of 256 x 256 65 us, 1536 of 128 x 128 55 us).
-constexpr double GELU_256 = 7.0, GELU_128 = 1.2;
-// The streaming kernel is considered up to MID_ROWS rows of activations, and up to
-// MID_ROWS_NARROW where 128 x 128 tiles would leave CUs without a workgroup: it reads its A tile
-// from LDS once per 32 MFMAs of a wave, and beyond that was never clearly the fastest measured
-// 16-bit plan (512 rows, 2048 -> 8192 columns: 27 us, tiles 32; 1500 rows, 768 -> 1536: 10.3 and
-// 11.8; 3000 rows: 16.1 and 13.9; four sub-layers of 2048 rows, 768 -> 768, 384 tiles: 25 and 18).
-constexpr int MID_ROWS = 512, MID_ROWS_NARROW = 1536;
-
-double cost_256(const TileCost& c, int64_t tiles, int64_t slices, double epi) {
-  return c.launch + (double)ceil_div(tiles, 256) * (c.round + epi + (double)slices * c.slice);
-}
-// two workgroups per CU; a last round that leaves every CU at most one of them runs its
-// slices faster (slice_half)
-double cost_128(const TileCost& c, int64_t tiles, int64_t slices, double epi) {
-  const int64_t full = tiles / 512, rem = tiles % 512;
-  double t = c.launch + (double)full * (c.round + epi + (double)slices * c.slice);
-  if (rem > 0) t += c.round + epi + (double)slices * (rem > 256 ? c.slice : c.slice_half);
-  return t;
-}
-double cost_mid(const TileCost& c, int64_t tiles, int64_t slices, int nb) {
-  return c.launch + (double)ceil_div(tiles, 256) *
-                        (c.round + (double)slices * (c.slice + c.slice_nb * nb));
-}
+constexpr TileCost COST16_256{0.0, 9.5, 1.0, 0, 0.63, 6.0, 4.0},
+    COST16_128{2.4, 0.9, 0.61, 0, 0.78, 3.1, 3.5},
+    COST16_MID{2.8, 1.3, 0.09, 0.093, 0.56, 1.9, 5.0};
+constexpr TileCost COST32_256{3.2, 7.4, 7.04, 0, 0.01, 2.0, 4.0},
+    COST32_128{0.0, 4.7, 1.71, 0, 1.05, 2.0, 3.5},
+    COST32_MID{3.1, 1.3, 0.083, 0.453, 0.08, 1.0, 5.0};
+// The streaming kernel is considered up to MID_ROWS rows of activations, past them where 128 x 128
+// tiles would fill at most half of the CUs (its tiles of 64 columns are then one round of
+// workgroups: 4059 rows, 1024 -> 256, 64 tiles: 11.0 us, 128 x 128 13.8; 2563 rows, 3072 -> 768, 126
+// tiles: 24.9 and 30.1), and up to MID_ROWS_NARROW (with a reduction of at most MID_SHORT
+// slices: any) where they would leave CUs without a workgroup: it reads its A tile from LDS once per
+// 32 MFMAs of a wave, and beyond that was never clearly the fastest measured 16-bit plan (512
+// rows, 2048 -> 8192 columns: 27 us, tiles 32; 1500 rows, 768 -> 1536: 10.3 and 11.8; 3000 rows:
+// 16.1 and 13.9; 4059 rows, 768 -> 768, 192 tiles: 15.0 and 12.9; 256 -> 256: 7.0 and 8.2).
+constexpr int MID_ROWS = 512, MID_ROWS_NARROW = 1536, MID_SHORT = 8;
 
 // A few rows (a decode step): whether the kernel for them is the faster one, and its form.
 // Measured with weights from HBM, fp16 (us; 16 columns x 4 waves per workgroup before):
@@ -56,19 +61,26 @@ double cost_mid(const TileCost& c, int64_t tiles, int64_t slices, int nb) {
 //   fp32      four of 4096 -> 1024 at 1 row 24.1 with 8 waves, 19.0 with 16; at 64 rows 48.5, the
 //             streaming kernel 70
 bool skinny_wins(bool f32, int M, int N, int64_t Kall, int batch, int64_t part_elems) {
-  if (M > 64) return false;
+  if (M > 64 || batch > 65535) return false;        // (the batch is a grid dimension)
   if (M <= 16 || f32) return true;
   // 17 to 32 rows: few columns and a reduction that is short or cannot be split
   return M <= 32 && (int64_t)N * batch <= 4096 && (Kall <= 2048 || part_elems == 0);
 }
 
-GemmPlan skinny_plan(bool f32, int M, int N, int64_t Kall, int batch) {
+GemmPlan skinny_plan(bool f32, int M, int N, int64_t Kall, int batch, int64_t part_elems,
+                     bool own_sum) {
   const int64_t blocks = ceil_div(N, 16) * batch;   // workgroups of one column block
   GemmPlan p{GemmKind::SKINNY, 1, 1, 4};
   if (f32 && M <= 16) p.waves = 16;
   else if (f32 || Kall >= 2048 || blocks <= 512) p.waves = 8;
   // two column blocks (each A fragment feeds two MFMAs) once they still fill the chip
   if (!f32 && M > 1 && blocks >= 1024 && Kall >= 2048) p.nb = 2;
+  // Few column blocks and a long reduction: K splits, as long as every wave keeps a whole batch
+  // of 8 steps.  A batch less per wave saves about 3 us; a launch for the sum costs 4.
+  const int64_t batches = Kall / (f32 ? 16 : 32) / (8 * p.waves);
+  const int64_t sp = std::min<int64_t>(
+      {8, 512 / blocks, batches, part_elems / ((int64_t)M * N * batch)});
+  if (sp > 1 && (!own_sum || 3 * (batches - batches / sp) > 6)) p.splits = (int)sp;
   return p;
 }
 
@@ -78,8 +90,8 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
                    int64_t part_elems, bool own_sum) {
   const bool f32 = dt == DType::F32;
   const int64_t Kall = (int64_t)K * kgroups;
-  if (epi != EPI_BIAS_M && epi != EPI_PART && skinny_wins(f32, M, N, Kall, batch, part_elems))
-    return skinny_plan(f32, M, N, Kall, batch);
+  if (epi != EPI_BIAS_M && skinny_wins(f32, M, N, Kall, batch, part_elems))
+    return skinny_plan(f32, M, N, Kall, batch, part_elems, own_sum);
   const int64_t slices = (int64_t)K / (f32 ? 32 : 64) * kgroups;
   const int64_t t256 = ceil_div(M, 256) * ceil_div(N, 256) * batch;
   const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128) * batch;
@@ -93,6 +105,7 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
   };
   const int64_t plane = (int64_t)M * N * batch;
   const int rows = epi == EPI_BIAS_M ? N : M;
+  const double wmb = (double)(epi == EPI_BIAS_M ? M : N) * (double)Kall * batch * (f32 ? 4e-6 : 2e-6);
   for (int sp = 1; sp <= 8; ++sp) {
     // Splits keep at least 8 slices each (2 of the four times longer fp32 ones; a shorter
     // reduction gains under 0.3 us per split); their planes must fit.  A plane costs about
@@ -104,17 +117,20 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
     double extra = 0.0;
     if (sp > 1) extra = 0.1 * mb * sp + 0.2 * mb * (sp - 1) + (own_sum ? 4.0 + 0.4 * mb : 0.0);
     const int64_t sl = ceil_div(slices, sp);
+    const bool gelu = epi == EPI_BIAS_N_GELU;
     consider(GemmKind::TILE256, 0, sp,
-             extra + cost_256(f32 ? COST32_256 : COST16_256, t256 * sp, sl,
-                              epi == EPI_BIAS_N_GELU ? GELU_256 : 0.0));
+             extra + (f32 ? COST32_256 : COST16_256).us(t256 * sp, 256, sl, 0, gelu, wmb));
+    // (two 128 x 128 workgroups per CU)
     consider(GemmKind::TILE128, 0, sp,
-             extra + cost_128(f32 ? COST32_128 : COST16_128, t128 * sp, sl,
-                              epi == EPI_BIAS_N_GELU ? GELU_128 : 0.0));
-    if (rows > (t128 * sp < 256 ? MID_ROWS_NARROW : MID_ROWS)) continue;
+             extra + (f32 ? COST32_128 : COST16_128).us(t128 * sp, 512, sl, 0, gelu, wmb));
+    const bool narrow = t128 * sp <= 128 ||
+                        (t128 * sp < 256 && (rows <= MID_ROWS_NARROW || slices <= MID_SHORT));
+    if (rows > MID_ROWS && !narrow) continue;
     for (int nb = 1; nb <= MID_MAX_NB; ++nb)
       consider(GemmKind::MID, nb, sp,
-               extra + cost_mid(f32 ? COST32_MID : COST16_MID,
-                                ceil_div(M, MID_BM) * ceil_div(N, 32 * nb) * batch * sp, sl, nb));
+               extra + (f32 ? COST32_MID : COST16_MID)
+                           .us(ceil_div(M, MID_BM) * ceil_div(N, 32 * nb) * batch * sp, 256, sl, nb,
+                               gelu, wmb));
   }
   return best;
 }
@@ -129,9 +145,10 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
   const int64_t es = (int64_t)dtype_size(g.dt);
   if ((int64_t)g.M * g.lda * es >= (1ll << 31) || (int64_t)g.N * g.ldb * es >= (1ll << 31))
     return hipErrorInvalidValue;
-  if (g.gA2 != 0 && (plan.kind != GemmKind::SKINNY || g.epi != EPI_BIAS_N_RES))
+  if (g.gA2 != 0 && (plan.kind != GemmKind::SKINNY ||
+                     (g.epi != EPI_BIAS_N_RES && g.epi != EPI_PART)))
     return hipErrorInvalidValue;
-  if (plan.kind == GemmKind::SKINNY && (g.M > 64 || g.epi == EPI_BIAS_M || g.epi == EPI_PART))
+  if (plan.kind == GemmKind::SKINNY && (g.M > 64 || g.epi == EPI_BIAS_M))
     return hipErrorInvalidValue;
   if (g.epi == EPI_QKV &&
       (!g.qkv || (plan.kind != GemmKind::SKINNY && plan.kind != GemmKind::MID) ||

@@ -74,9 +74,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p, QkvA
     return v;
   };
   auto load_b = [&](int w, int64_t off) { return *reinterpret_cast<const uint4*>(Bz[w] + off); };
+  // this wave's steps: the workgroup's K split (EPI_PART: p.splits of them), then its waves
   const int steps_per_group = p.K / KS;
-  const int steps = steps_per_group * p.kgroups;
-  const int t0 = (int)((int64_t)steps * wave / NW), t1 = (int)((int64_t)steps * (wave + 1) / NW);
+  const int64_t steps = (int64_t)steps_per_group * p.kgroups;
+  const int sp = EPI == EPI_PART ? blockIdx.z : 0, parts = NW * (EPI == EPI_PART ? p.splits : 1);
+  const int t0 = (int)(steps * (sp * NW + wave) / parts);
+  const int t1 = (int)(steps * (sp * NW + wave + 1) / parts);
   f32x4 acc[MB * TW];
 #pragma unroll
   for (int q = 0; q < MB * TW; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -92,28 +95,29 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p, QkvA
       if (++gb == p.gBmod) gb = 0;
     }
   };
-  int t = t0;
-  for (; t + SK_UNROLL <= t1; t += SK_UNROLL) {
-    uint4 bv[SK_UNROLL][TW], av[SK_UNROLL][MB * NA];
-    int64_t ao[SK_UNROLL], bo[SK_UNROLL];
+  // n steps, all their loads issued together
+  auto batch = [&](auto Nc) {
+    constexpr int U = decltype(Nc)::value;
+    uint4 bv[U][TW], av[U][MB * NA];
+    int64_t ao[U], bo[U];
 #pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u) {
+    for (int u = 0; u < U; ++u) {
       ao[u] = g * p.gA + kk;
       bo[u] = gb * p.gB + kk;
       advance();
     }
 #pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int w = 0; w < TW; ++w) bv[u][w] = load_b(w, bo[u]);
 #pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int q = 0; q < NA; ++q) av[u][mb * NA + q] = load_a(mb, ao[u] + q * p.gA2);
 #pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int q = 0; q < NA; ++q)
 #pragma unroll
@@ -121,22 +125,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p, QkvA
 #pragma unroll
           for (int w = 0; w < TW; ++w)
             acc[mb * TW + w] = mfma16<S>(av[u][mb * NA + q], bv[u][w], acc[mb * TW + w]);
-  }
-  for (; t < t1; ++t) {
-    uint4 bv[TW];
-#pragma unroll
-    for (int w = 0; w < TW; ++w) bv[w] = load_b(w, gb * p.gB + kk);
-    const int64_t ao = g * p.gA + kk;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int q = 0; q < NA; ++q) {
-        const uint4 av = load_a(mb, ao + q * p.gA2);
-#pragma unroll
-        for (int w = 0; w < TW; ++w) acc[mb * TW + w] = mfma16<S>(av, bv[w], acc[mb * TW + w]);
-      }
-    advance();
-  }
+  };
+  int t = t0;
+  for (; t + SK_UNROLL <= t1; t += SK_UNROLL) batch(I<SK_UNROLL>{});
+  // the remainder in batches of 4, 2 and 1 (step by step, a wave with 7 steps waits 7 times)
+  if ((t1 - t) & 4) batch(I<4>{});
+  if ((t1 - t) & 2) batch(I<2>{});
+  if ((t1 - t) & 1) batch(I<1>{});
   // D row 4 kq + j, column col of each 16-row block -> red[wave][mb][row * 16 + col]
 #pragma unroll
   for (int q = 0; q < MB * TW; ++q)
@@ -157,7 +152,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p, QkvA
     for (int d = 1; d < NW; d <<= 1)
 #pragma unroll
       for (int k = 0; k + d < NW; k += 2 * d) part[k] += part[k + d];
-    float v = part[0] + (biasz ? biasz[n] : 0.f);
+    float v = part[0] + (EPI != EPI_PART && biasz ? biasz[n] : 0.f);
     if constexpr (EPI == EPI_BIAS_N_GELU) v = gelu_erf(v);
     if constexpr (epi_res<EPI>) {
       if (p.R) v += p.R[z * p.sR + (int64_t)m * p.ldc + n];
@@ -174,7 +169,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(GemmParams p, QkvA
         continue;
       }
     }
-    OutT* dst = static_cast<OutT*>(p.C) + z * p.sC + (int64_t)m * p.ldc + n;
+    OutT* dst = static_cast<OutT*>(p.C) + z * p.sC + (int64_t)m * p.ldc + n +
+                (EPI == EPI_PART ? sp * p.sPlane : 0);
     store_val<OutT>(dst, v);
     if constexpr (EPI == EPI_BIAS_N_HILO) store_val<OutT>(dst + p.sPlane, v - (float)(S)v);
   }
@@ -185,7 +181,7 @@ template <typename S, int MB, int TW, int NW>
 hipError_t launch_skinny(const GemmDesc& g, hipStream_t s) {
   GemmParams p = gemm_params(g);
   p.tiles_n = (g.N + 16 * TW - 1) / (16 * TW);
-  const dim3 grid((unsigned)p.tiles_n, (unsigned)g.batch), block(64 * NW);
+  const dim3 grid((unsigned)p.tiles_n, (unsigned)g.batch, (unsigned)p.splits), block(64 * NW);
   switch (g.epi) {
     case EPI_BIAS_N:
       hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_BIAS_N, false>), grid, block, 0,
@@ -213,6 +209,17 @@ hipError_t launch_skinny(const GemmDesc& g, hipStream_t s) {
         break;
       }
       return hipErrorInvalidValue;
+    case EPI_PART:
+      if constexpr (sizeof(S) == 2) {
+        if (g.gA2 != 0) {
+          hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_PART, true>), grid, block, 0, s,
+                             p, qkv_arg<EPI_PART>(g));
+          break;
+        }
+      }
+      hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_PART, false>), grid, block, 0, s, p,
+                         qkv_arg<EPI_PART>(g));
+      break;
     case EPI_QKV:
       hipLaunchKernelGGL((gemm_skinny_kernel<S, MB, TW, NW, EPI_QKV, false>), grid, block, 0, s, p,
                          qkv_arg<EPI_QKV>(g));

@@ -105,7 +105,7 @@ struct GemmDesc {
   // elements from the high to the low terms
   int splits;
   int64_t sPlane;
-  // SKINNY with EPI_BIAS_N_RES: != 0 adds a second term of A, gA2 elements behind the first,
+  // SKINNY with EPI_BIAS_N_RES or EPI_PART: != 0 adds a second term of A, gA2 elements behind the first,
   // multiplied by the same B
   int64_t gA2;
   const QkvOut* qkv;        // EPI_QKV (host memory, read by the launch)

@@ -542,8 +542,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // together and their planes summed as one, or neither is.
   const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
   const int64_t room = parallel ? m->part_elems / 2 : m->part_elems;
-  GemmPlan plan_o = plan_gemm(dt, parallel ? EPI_PART : EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1,
-                              (int)N, room, false);
+  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, room, false);
   GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N, room, false);
   const GemmPlan plan_o_whole =
       plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, 0, false);

@@ -47,9 +47,8 @@ def test_plans_stay_within_their_limits():
         part = rng.choice([0, M * N * b, 5 * M * N * b, 1 << 40])
         epi = rng.choice([RES, RES, PART])
         p = plan(dt, epi, M, N, K, g, b, part, rng.random() < 0.5)
-        assert epi != PART or p.kind != SKINNY
         assert p.kind != SKINNY or M <= 64
-        assert p.kind == SKINNY or epi == PART or M > (64 if dt == F32 else 16)
+        assert p.kind == SKINNY or M > (64 if dt == F32 else 16)
         waves = (4, 8, 16) if M <= 16 and dt == F32 else (4, 8)
         assert p.kind != SKINNY or (p.nb in (1, 2) and p.waves in waves)
         assert p.kind != MID or 1 <= p.nb <= 6
@@ -126,20 +125,22 @@ FEW_ROWS = [(1, 300, 64, 2), (5, 1000, 2048, 3), (16, 64, 8192, 1), (17, 33, 320
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dual", [False, True])
-@pytest.mark.parametrize("epi", [BIAS_N, GELU, RES, HILO])
+@pytest.mark.parametrize("epi", [BIAS_N, GELU, RES, HILO, PART])
 @pytest.mark.parametrize("dt", [F32, BF16, F16])
 def test_every_few_row_plan(dt, epi, dual):
-    if dt == F32 and (epi == HILO or dual) or dual and epi != RES:
+    if dt == F32 and (epi == HILO or dual) or dual and epi not in (RES, PART):
         pytest.skip("not a kernel")
     f = getattr(_lib(), "_ZN6kraken19launch_gemm_plannedERKNS_8GemmDescERKNS_8GemmPlanEP12ihipStream_t")
     f.restype = I
     S = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[dt]
-    out = torch.float32 if epi == RES else S
+    out = torch.float32 if epi in (RES, PART) else S
     # as above
     tol = {torch.float32: 1e-5, torch.float16: 4e-4, torch.bfloat16: 3.2e-3}[out]
     if epi == HILO:
         tol = {BF16: 2e-5, F16: 1e-6}[dt]
     for M, N, K, batch in FEW_ROWS:
+        if epi == PART and K < 256:        # fewer slices than splits are refused
+            continue
         g = torch.Generator(device="cuda").manual_seed(M + N + K)
         # two terms of A: the second one is the kernel's only where it reads two
         A = torch.randn((2, batch, M, K), generator=g, device="cuda").to(S)
@@ -147,20 +148,22 @@ def test_every_few_row_plan(dt, epi, dual):
         bias = torch.randn((batch, N), generator=g, device="cuda")
         R = torch.randn((batch, M, N), generator=g, device="cuda")
         a64 = A.double().sum(0) if dual else A[0].double()
-        ref = torch.stack([a @ b.T for a, b in zip(a64, B.double())]) + bias.double()[:, None]
+        ref = torch.stack([a @ b.T for a, b in zip(a64, B.double())])
+        if epi != PART:
+            ref = ref + bias.double()[:, None]
+        planes = 3 if epi == PART else 2 if epi == HILO else 1
         if epi == GELU:
             ref = torch.nn.functional.gelu(ref)
         if epi in (RES, HILO):
             ref = ref + R.double()
         d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
-                 K, K, N, M * K, N * K, M * N, M * N, N, batch, 1, 0, 0, 1, 1, batch * M * N,
+                 K, K, N, M * K, N * K, M * N, M * N, N, batch, 1, 0, 0, 1, 3 if epi == PART else 1, batch * M * N,
                  batch * M * K if dual else 0, None, None)
         for tw in (1, 2):
             for waves in (4, 8, 16) if M <= 16 and dt == F32 else (4, 8):
-                C = torch.full((2 if epi == HILO else 1, batch, M, N), float("nan"), dtype=out,
-                               device="cuda")
+                C = torch.full((planes, batch, M, N), float("nan"), dtype=out, device="cuda")
                 d.C = C.data_ptr()
-                rc = f(ctypes.byref(d), ctypes.byref(Plan(SKINNY, tw, 1, waves)),
+                rc = f(ctypes.byref(d), ctypes.byref(Plan(SKINNY, tw, d.splits, waves)),
                        P(torch.cuda.current_stream().cuda_stream or None))
                 assert rc == 0
                 torch.cuda.synchronize()
