@@ -111,8 +111,12 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
     // reduction gains under 0.3 us per split); their planes must fit.  A plane costs about
     // 0.1 us per MB to write and 0.2 us per MB to read in the kernel that sums them, which
     // without a split would read one as well, unless it is launched for the sum alone (4 us,
-    // and its result and residual pass through it too).
-    if (sp > 1 && (sp * plane > part_elems || slices < (f32 ? 2 : 8) * sp)) break;
+    // and its result and residual pass through it too).  A launch for the sum alone is not spent
+    // where 128 x 128 tiles fill the chip: W_concat then reduces in one order from some thousand
+    // rows on, and a prefix of a prompt has the bits of the whole.
+    if (sp > 1 && (sp * plane > part_elems || slices < (f32 ? 2 : 8) * sp ||
+                   (own_sum && t128 >= 512)))
+      break;
     const double mb = (double)plane * 4e-6;
     double extra = 0.0;
     if (sp > 1) extra = 0.1 * mb * sp + 0.2 * mb * (sp - 1) + (own_sum ? 4.0 + 0.4 * mb : 0.0);

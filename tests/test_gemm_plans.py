@@ -63,6 +63,7 @@ def test_large_prompts_keep_their_rows_independent_of_the_length():
     for M in (4096, 8192):
         for N, K in ((4096, 2048), (2048, 2048), (8192, 2048), (2048, 8192)):
             assert plan(F16, RES, M, N, K, 1, 8, 1 << 26).splits == 1
+        assert plan(F16, RES, M, 2048, 2048, 16, 1, 1 << 26, True).splits == 1    # W_concat
 
 
 # (M, N, K, batch, K splits): one row past and short of tiles of 128 and 256, column counts
