@@ -57,8 +57,8 @@ TRAFFIC = {
     # FFN up projection with the GELU epilogue (A: LN2 output, B: W1, C: the activation)
     "gemm_up": {
         "source": "paper_2408_07802_amd/csrc/gemm_tile.hip",
-        "source_sha256": "f1dc93bcb808f68ffd6bc0aa3c4dbb47aca788a565382196412281b4cd55520d",
-        "read_bytes": 3224337862, "write_bytes": 1074022680,
+        "source_sha256": "bb50799ce9199d49e4758477fb8b7b5a4d5a5f10776bcfd45f7a2477e74795c0",
+        "read_bytes": 3224320361, "write_bytes": 1073965163,
         "algorithmic_bytes": 2 * (8 * 8192 * 2048 * 2 + 8 * 8192 * 8192) + 8 * 8192 * 4,
         "profile": "profiles/hbm_traffic_n8_l24_d2048_t8192.md",
     },

@@ -35,19 +35,23 @@ struct TileCost {
 };
 constexpr TileCost COST16_256{0.0, 9.5, 1.0, 0, 0.63, 6.0, 4.0},
     COST16_128{2.4, 0.9, 0.61, 0, 0.78, 3.1, 3.5},
+    COST16_64{2.4, 0.6, 0.42, 0, 0.6, 1.6, 3.5},   // 128 x 64 tiles
     COST16_MID{2.8, 1.3, 0.09, 0.093, 0.56, 1.9, 5.0};
 constexpr TileCost COST32_256{3.2, 7.4, 7.04, 0, 0.01, 2.0, 4.0},
     COST32_128{0.0, 4.7, 1.71, 0, 1.05, 2.0, 3.5},
     COST32_MID{3.1, 1.3, 0.083, 0.453, 0.08, 1.0, 5.0};
-// The streaming kernel is considered up to MID_ROWS rows of activations, past them where 128 x 128
-// tiles would fill at most half of the CUs (its tiles of 64 columns are then one round of
-// workgroups: 4059 rows, 1024 -> 256, 64 tiles: 11.0 us, 128 x 128 13.8; 2563 rows, 3072 -> 768, 126
-// tiles: 24.9 and 30.1), and up to MID_ROWS_NARROW (with a reduction of at most MID_SHORT
-// slices: any) where they would leave CUs without a workgroup: it reads its A tile from LDS once per
-// 32 MFMAs of a wave, and beyond that was never clearly the fastest measured 16-bit plan (512
-// rows, 2048 -> 8192 columns: 27 us, tiles 32; 1500 rows, 768 -> 1536: 10.3 and 11.8; 3000 rows:
-// 16.1 and 13.9; 4059 rows, 768 -> 768, 192 tiles: 15.0 and 12.9; 256 -> 256: 7.0 and 8.2).
-constexpr int MID_ROWS = 512, MID_ROWS_NARROW = 1536, MID_SHORT = 8;
+// The streaming kernel is considered up to MID_ROWS rows of activations, and past them where
+// 128 x 128 tiles would leave CUs without a workgroup: up to MID_ROWS_NARROW rows (with a
+// reduction of at most MID_SHORT slices, or at most half of the CUs taken: up to MID_ROWS_LAST).  It
+// reads its A tile from LDS once per 32 MFMAs of a wave, and beyond that was never clearly the
+// fastest measured 16-bit plan (512 rows, 2048 -> 8192 columns: 27 us, tiles 32; 1500 rows,
+// 768 -> 1536: 10.3 and 11.8; 1800 rows, 3072 -> 768: 21.3 and 30.5; 3000 rows, 768 -> 1536: 16.1
+// and 13.9).  Past MID_ROWS_LAST rows 128 x 64 tiles, two workgroups per CU, take its place there (4713
+// rows, 1536 -> 384: 16.4 us, streaming 17.1, 128 x 128 19.6; 384 -> 384: 7.2, 7.7 and 9.8; 4059
+// rows, 768 -> 768: 11.8, 15.0 and 12.8; 2563 rows, 3072 -> 768: 26.0, 26.7 and 29.8).  fp32
+// is bound by its MFMAs and takes the streaming kernel at any number of rows (4059 rows,
+// 768 -> 768: 47.1 us, 128 x 128 56.1).
+constexpr int MID_ROWS = 512, MID_ROWS_NARROW = 1536, MID_ROWS_LAST = 2560, MID_SHORT = 8;
 
 // A few rows (a decode step): whether the kernel for them is the faster one, and its form.
 // Measured with weights from HBM, fp16 (us; 16 columns x 4 waves per workgroup before):
@@ -127,9 +131,16 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
     // (two 128 x 128 workgroups per CU)
     consider(GemmKind::TILE128, 0, sp,
              extra + (f32 ? COST32_128 : COST16_128).us(t128 * sp, 512, sl, 0, gelu, wmb));
-    const bool narrow = t128 * sp <= 128 ||
-                        (t128 * sp < 256 && (rows <= MID_ROWS_NARROW || slices <= MID_SHORT));
-    if (rows > MID_ROWS && !narrow) continue;
+    const bool narrow = t128 * sp < 256;
+    if (!f32 && narrow && rows > MID_ROWS_LAST)
+      consider(GemmKind::TILE128, 2, sp,
+               extra + COST16_64.us(ceil_div(M, 128) * ceil_div(N, 64) * batch * sp, 512, sl, 0,
+                                    gelu, wmb));
+    const bool mid = rows <= MID_ROWS ||
+                     (narrow && (f32 || rows <= MID_ROWS_NARROW ||
+                                 (rows <= MID_ROWS_LAST &&
+                                  (t128 * sp <= 128 || slices <= MID_SHORT))));
+    if (!mid) continue;
     for (int nb = 1; nb <= MID_MAX_NB; ++nb)
       consider(GemmKind::MID, nb, sp,
                extra + (f32 ? COST32_MID : COST16_MID)
@@ -167,11 +178,12 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
       return g.dt == DType::BF16 ? launch_gemm_mid<bf16>(g, plan.nb, s)
              : g.dt == DType::F16 ? launch_gemm_mid<f16>(g, plan.nb, s)
                                   : launch_gemm_mid<float>(g, plan.nb, s);
-    default:
-      return g.dt == DType::BF16 ? launch_gemm_tile<bf16>(g, plan.kind == GemmKind::TILE256, s)
-             : g.dt == DType::F16
-                 ? launch_gemm_tile<f16>(g, plan.kind == GemmKind::TILE256, s)
-                 : launch_gemm_tile<float>(g, plan.kind == GemmKind::TILE256, s);
+    default: {
+      const int cols = plan.kind == GemmKind::TILE256 ? 256 : plan.nb == 2 ? 64 : 128;
+      return g.dt == DType::BF16 ? launch_gemm_tile<bf16>(g, cols, s)
+             : g.dt == DType::F16 ? launch_gemm_tile<f16>(g, cols, s)
+                                  : launch_gemm_tile<float>(g, cols, s);
+    }
   }
 }
 

@@ -521,8 +521,12 @@ hipError_t launch_cfg(const GemmDesc& g, hipStream_t s) {
 }  // namespace
 
 template <>
-hipError_t launch_gemm_tile<KRAKEN_T>(const GemmDesc& g, bool big, hipStream_t s) {
-  return big ? launch_cfg<KRAKEN_T, 256, 256>(g, s) : launch_cfg<KRAKEN_T, 128, 128>(g, s);
+hipError_t launch_gemm_tile<KRAKEN_T>(const GemmDesc& g, int cols, hipStream_t s) {
+  if (cols == 256) return launch_cfg<KRAKEN_T, 256, 256>(g, s);
+  if (cols == 128) return launch_cfg<KRAKEN_T, 128, 128>(g, s);
+  if constexpr (sizeof(KRAKEN_T) == 2)
+    if (cols == 64) return launch_cfg<KRAKEN_T, 128, 64>(g, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace kraken

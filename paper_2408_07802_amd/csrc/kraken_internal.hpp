@@ -120,7 +120,8 @@ hipError_t launch_gemm(const GemmDesc& g, hipStream_t s);
 enum class GemmKind : int { TILE256, TILE128, MID, SKINNY };
 struct GemmPlan {
   GemmKind kind;
-  int nb;       // MID: 32-column blocks per tile; SKINNY: 16-column blocks per workgroup (1, 2)
+  int nb;       // MID: 32-column blocks per tile; SKINNY: 16-column blocks per workgroup (1, 2);
+                // TILE128: 2 for tiles of 64 columns (16-bit operands), else 0
   int splits;   // K splits
   int waves;    // SKINNY: waves that share a workgroup's reduction (4, 8; 16 for fp32
                 // up to 16 rows)
@@ -134,7 +135,7 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
 hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStream_t s);
 // The kernels of the plans TILE256 / TILE128, MID and SKINNY (one object file per operand type).
 template <typename S>
-hipError_t launch_gemm_tile(const GemmDesc& g, bool big, hipStream_t s);
+hipError_t launch_gemm_tile(const GemmDesc& g, int cols, hipStream_t s);
 template <typename S>
 hipError_t launch_gemm_mid(const GemmDesc& g, int nb, hipStream_t s);
 template <typename S>
@@ -142,9 +143,9 @@ hipError_t launch_gemm_skinny(const GemmDesc& g, int tw, int nw, hipStream_t s);
 template <> hipError_t launch_gemm_skinny<bf16>(const GemmDesc&, int, int, hipStream_t);
 template <> hipError_t launch_gemm_skinny<f16>(const GemmDesc&, int, int, hipStream_t);
 template <> hipError_t launch_gemm_skinny<float>(const GemmDesc&, int, int, hipStream_t);
-template <> hipError_t launch_gemm_tile<bf16>(const GemmDesc&, bool, hipStream_t);
-template <> hipError_t launch_gemm_tile<f16>(const GemmDesc&, bool, hipStream_t);
-template <> hipError_t launch_gemm_tile<float>(const GemmDesc&, bool, hipStream_t);
+template <> hipError_t launch_gemm_tile<bf16>(const GemmDesc&, int, hipStream_t);
+template <> hipError_t launch_gemm_tile<f16>(const GemmDesc&, int, hipStream_t);
+template <> hipError_t launch_gemm_tile<float>(const GemmDesc&, int, hipStream_t);
 template <> hipError_t launch_gemm_mid<bf16>(const GemmDesc&, int, hipStream_t);
 template <> hipError_t launch_gemm_mid<f16>(const GemmDesc&, int, hipStream_t);
 template <> hipError_t launch_gemm_mid<float>(const GemmDesc&, int, hipStream_t);

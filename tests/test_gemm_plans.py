@@ -88,6 +88,8 @@ def test_every_plan_at_tile_edges(dt, epi):
     if epi == HILO:
         tol = {BF16: 2e-5, F16: 1e-6}[dt]     # (2^-8)^2, and (2^-11)^2 with fp32 sums
     plans = [(TILE256, 0), (TILE128, 0)] + [(MID, nb) for nb in range(1, 7)]
+    if dt != F32:
+        plans.append((TILE128, 2))            # 128 x 64
     for M, N, K, batch, splits in SHAPES:
         if epi == HILO and N % 4:
             N += 4 - N % 4
