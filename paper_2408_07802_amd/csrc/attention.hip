@@ -206,14 +206,16 @@ __device__ __forceinline__ float sum8<bf16>(uint4 v, float acc) {
 // NQB 32-query blocks per wave: NQB = 1 runs 8 waves (two per SIMD, so one wave's
 // softmax arithmetic overlaps the other's matrix work); NQB = 2 runs 4 waves.
 //
-// PRE (16-bit operands whose Q already carries log2(e) / sqrt(hd)): the softmax of the
-// ping-pong form below, i.e. scores accumulate onto -c0 so that a weight is a bare exp2, row
-// sums add the packed weights, and the row maximum is computed only on tiles that can need a
-// new exponent base.  These kernels are bound by their VALU work (heads of 64: 32 exponentials
-// a tile against 16 MFMAs).  Measured, fp16: 17228 tokens in 8 sequences, 4 x 20 heads of 64
-// 666-760 -> 620 us; 4096 tokens, 16 heads of 64 over 4 81 -> 76 us; 1500 tokens, 8 x 32 heads of
-// 32 98 -> 92 us.  (The launch bound keeps heads of 64 at two workgroups per CU; with -c0 kept in
-// 16 registers as in the ping-pong form that costs 80 bytes of spills per lane, 892 us.)
+// PRE (16-bit operands whose Q already carries log2(e) / sqrt(hd)): scores accumulate onto -c0,
+// so a weight is a bare exp2 without a multiplication.  The row sums add the fp32 weights, as in
+// the plain form.  These kernels are bound by their VALU work (heads of 64: 32 exponentials a
+// tile against 16 MFMAs).  Heads of 32 also skip the row maximum on tiles that cannot need a new
+// exponent base; for heads of 64 that costs registers (48 bytes of spills per lane).  Measured,
+// us, plain form / maxima always / maxima where needed: fp16, 17228 tokens in 8 sequences, 4 x
+// 20 heads of 64 651-676 / 620 / 716; 4096 tokens, 16 heads of 64 over 4 79 / 73 / 101; bf16, 2048
+// tokens, 4 x 12 heads of 64 46 / 44 / 56; fp16, 1500 tokens, 8 x 32 heads of 32 96-99 / 98 /
+// 87-91; 4096 tokens, 2 x 16 heads of 32 95 / 96 / 88.  (The launch bound keeps heads of 64 at two
+// workgroups per CU.)
 template <typename S, int HD, int NQB, bool PRE>
 __global__ __launch_bounds__(BQ / NQB / 32 * 64, HD == 64 && sizeof(S) == 2 ? 4 : 1)
 void attn_kernel(AttnParams p) {
@@ -399,46 +401,53 @@ void attn_kernel(AttnParams p) {
       };
       if constexpr (PRE) {
         typedef S s8 __attribute__((ext_vector_type(8)));
-        float lsum[4];
+        float lsum;                             // of the fp32 weights, before P is rounded
         auto weights = [&]() {
+          lsum = 0.f;
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
               s8 v;
 #pragma unroll
-              for (int j = 0; j < 8; ++j)
-                v[j] = (S)__builtin_amdgcn_exp2f(st[qb][sb][8 * hh + j]);
+              for (int j = 0; j < 8; ++j) {
+                const float e = __builtin_amdgcn_exp2f(st[qb][sb][8 * hh + j]);
+                v[j] = (S)e;
+                lsum += e;
+              }
               pb[qb][sb][hh] = __builtin_bit_cast(uint4, v);
-              lsum[2 * sb + hh] = sum8<S>(pb[qb][sb][hh], 0.f);
             }
         };
-        // (attn_pp_kernel's vector phase states why the shortcut decides alike)
-        bool exact = t == 0;
-        if (!exact) {
-          weights();
-          exact = __ballot((lsum[0] + lsum[1]) + (lsum[2] + lsum[3]) >= 256.0f) != 0;
-        }
-        if (exact) {
+        // moves the exponent base if some lane's maximum exceeds it by more than 8; true if so
+        auto rebase = [&]() {
           const float mx = row_max();
-          if (__ballot(mx > m_run[qb] + 8.0f)) {
-            const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - mx);
-            l_run[qb] *= alpha;
+          if (!__ballot(mx > m_run[qb] + 8.0f)) return false;
+          const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - mx);
+          l_run[qb] *= alpha;
 #pragma unroll
-            for (int ob = 0; ob < OB; ++ob)
+          for (int ob = 0; ob < OB; ++ob)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) oacc[qb][ob][r] *= alpha;
-            const float shift = mx - c0[qb];
+            for (int r = 0; r < 16; ++r) oacc[qb][ob][r] *= alpha;
+          const float shift = mx - c0[qb];
 #pragma unroll
-            for (int sb = 0; sb < 2; ++sb)
+          for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) st[qb][sb][r] -= shift;
-            c0[qb] = mx;
-            m_run[qb] = mx;
-          }
+            for (int r = 0; r < 16; ++r) st[qb][sb][r] -= shift;
+          c0[qb] = mx;
+          m_run[qb] = mx;
+          return true;
+        };
+        if constexpr (HD == 32) {
+          // A maximum more than 8 above the base would show in the sum: no maximum is taken
+          // below 2^8 (attn_pp_kernel's vector phase has the argument).
+          weights();
+          if (t == 0 || __ballot(lsum >= 256.0f))
+            if (rebase()) weights();
+        } else {
+          rebase();
           weights();
         }
-        l_run[qb] += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
+        l_run[qb] += lsum;
         continue;
       }
       const float mx = row_max();

@@ -424,8 +424,20 @@ def test_attention_rising_scores_take_every_softmax_path(dtype, pre):
     tiles in between have packed row sums of 2^8 or more while staying within 8 of the
     base (the exact path, which then keeps the base); the low tail takes the shortcut
     without a maximum.  Every query sees the same profile up to its own position."""
-    n, d, H, T = 1, 256, 2, 1700
-    hd = d // H
+    rising_scores(dtype, pre, 128)
+
+
+@pytest.mark.parametrize("hd", [64, 32])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_attention_rising_scores_in_the_one_phase_kernel(dtype, hd):
+    """The same for smaller heads, whose one-phase kernel takes the same three paths when Q is
+    pre-scaled."""
+    rising_scores(dtype, True, hd)
+
+
+def rising_scores(dtype, pre, hd):
+    n, H, T = 1, 2, 1700
+    d = H * hd
     cu = [0, T]
     dt = tdt(dtype)
     g = torch.Generator(device="cpu").manual_seed(77)
@@ -449,6 +461,44 @@ def test_attention_rising_scores_take_every_softmax_path(dtype, pre):
     q64 = qk[0, :, :d].double().numpy() / (c if pre else 1.0)
     check_heads(f64(out[0]), q64, qk[0, :, d:].double().numpy(), v[0].double().numpy(), cu,
                 H, None, dtype, "attention with rising scores")
+
+
+@pytest.mark.parametrize("hd", [64, 32])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_attention_one_phase_row_sums_add_weights_in_fp32(dtype, hd):
+    """Every key but the first has a weight of (1 + 0.9 u) / 2, u half a unit in the last place
+    of 1 in the operand type: rounded to the operand type it is 1/2, for every key alike, so a
+    denominator that adds rounded weights is low by 0.9 u of nearly all of its terms.  Only
+    the first key (weight 1) has values, so the numerator is exact and an output is
+    v / (1 + t (1 + 0.9 u) / 2).  Rounding the outputs (to nearest, either way) gives each a
+    relative error within u; over 2 x hd x 1400 of them the mean is within u / 100 of zero, and
+    a denominator of rounded weights moves it by 0.9 u."""
+    n, H, T = 1, 2, 1500
+    d, cu, dt = H * hd, [0, T], tdt(dtype)
+    u = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]
+    low = math.log2(1 + 0.9 * u)                  # a key's score is -1 + low, in log2 units
+    q = torch.zeros((n, T, d))
+    k = torch.zeros((n, T, d))
+    for h in range(H):
+        q[:, :, h * hd:h * hd + 2] = 1.0
+        k[:, 1:, h * hd] = -1.0
+        k[:, 1:, h * hd + 1] = low
+    qk = torch.cat([q.to(dt), k.to(dt)], dim=2)
+    low = float(qk[0, 1, d + 1])                  # as the operand type holds it
+    assert 0.8 * u < 2 ** low - 1 < u
+    g = torch.Generator(device="cpu").manual_seed(5)
+    v = (1 + torch.rand(d, generator=g)).to(dt)
+    vt = torch.zeros((n, d, K().vt_ld(T)), dtype=dt)
+    vt[0, :, 0] = v
+    out = torch.full((n, T, d), float("nan"), dtype=dt, device=DEV)
+    K().op_attention(qk.to(DEV), vt.to(DEV), out, n, d, H, cu, q_prescaled=True)
+    torch.cuda.synchronize()
+    t = np.arange(T)[:, None]
+    ref = v.double().numpy() / (1 + t * 2.0 ** (low - 1))
+    rel = (f64(out[0]) / ref - 1)[100:]
+    print(f"    mean relative error {rel.mean() / u:+.4f} u, largest {np.abs(rel).max() / u:.3f} u",
+          flush=True)
+    assert abs(rel.mean()) <= 0.1 * u
 
 
 def test_attention_dma_base_with_bit31_of_the_low_address_word_set_and_clear():
