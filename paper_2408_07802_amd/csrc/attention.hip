@@ -211,13 +211,15 @@ __device__ __forceinline__ float sum8<bf16>(uint4 v, float acc) {
 // the plain form.  These kernels are bound by their VALU work (heads of 64: 32 exponentials a
 // tile against 16 MFMAs).  Heads of 32 also skip the row maximum on tiles that cannot need a new
 // exponent base; for heads of 64 that costs registers (48 bytes of spills per lane).  Measured,
-// us, plain form / maxima always / maxima where needed: fp16, 17228 tokens in 8 sequences, 4 x
-// 20 heads of 64 651-676 / 620 / 716; 4096 tokens, 16 heads of 64 over 4 79 / 73 / 101; bf16, 2048
-// tokens, 4 x 12 heads of 64 46 / 44 / 56; fp16, 1500 tokens, 8 x 32 heads of 32 96-99 / 98 /
-// 87-91; 4096 tokens, 2 x 16 heads of 32 95 / 96 / 88.  (The launch bound keeps heads of 64 at two
-// workgroups per CU.)
+// us, plain form / this one: fp16, 17228 tokens in 8 sequences, 4 x 20 heads of 64 651-676 / 620
+// (maxima where needed: 716); 4096 tokens, 16 heads of 64 over 4 79 / 73 (101); bf16, 2048 tokens,
+// 4 x 12 heads of 64 46 / 44 (56); fp16, 1500 tokens, 8 x 32 heads of 32 96 / 76; 4096 tokens, 2 x
+// 16 heads of 32 95 / 71.
+// The launch bound (waves per SIMD) keeps heads of 64 and of 32 at two workgroups per CU; left to
+// itself the compiler gives heads of 32 270 registers, one workgroup: 1500 tokens 135 us.
 template <typename S, int HD, int NQB, bool PRE>
-__global__ __launch_bounds__(BQ / NQB / 32 * 64, HD == 64 && sizeof(S) == 2 ? 4 : 1)
+__global__
+__launch_bounds__(BQ / NQB / 32 * 64, sizeof(S) == 4 ? 1 : HD == 64 ? 4 : HD == 32 ? 2 : 1)
 void attn_kernel(AttnParams p) {
   constexpr int QW = 32 * NQB;                // queries per wave
   constexpr int NW = BQ / QW;                 // waves per workgroup
