@@ -322,11 +322,14 @@ void attn_kernel(AttnParams p) {
       for (int r = 0; r < 16; ++r) oacc[qb][ob][r] = 0.f;
   float m_run[NQB], l_run[NQB];
   float c0[NQB];                              // (PRE) the S accumulators start from -c0
+  uint64_t baseless[NQB];                     // (PRE) lanes without a finite score so far
+  constexpr float NO_MAX = -1e30f;
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
-    m_run[qb] = -1e30f;
+    m_run[qb] = NO_MAX;
     l_run[qb] = 0.f;
     c0[qb] = 0.f;
+    baseless[qb] = ~0ull;
   }
 
   const int n_tiles = (q_hi - kv_begin + BKV - 1) / BKV;
@@ -430,21 +433,27 @@ void attn_kernel(AttnParams p) {
           for (int ob = 0; ob < OB; ++ob)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[qb][ob][r] *= alpha;
-          const float shift = mx - c0[qb];
+          // (a query whose scores were all -inf so far has no base yet: were c0 its maximum of
+          // -1e30, the scores of the next tile would vanish beside it)
+          const float base = mx == NO_MAX ? 0.f : mx;
+          const float shift = base - c0[qb];
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) st[qb][sb][r] -= shift;
-          c0[qb] = mx;
+          c0[qb] = base;
           m_run[qb] = mx;
           return true;
         };
         if constexpr (HD == 32) {
-          // A maximum more than 8 above the base would show in the sum: no maximum is taken
-          // below 2^8 (attn_pp_kernel's vector phase has the argument).
+          // A maximum more than 8 above the base would show in the sum: once every lane has a
+          // base, no maximum is taken below 2^8 (attn_pp_kernel's vector phase has the
+          // argument).
           weights();
-          if (t == 0 || __ballot(lsum >= 256.0f))
+          if (baseless[qb] | __ballot(lsum >= 256.0f)) {
             if (rebase()) weights();
+            baseless[qb] = __ballot(m_run[qb] == NO_MAX);
+          }
         } else {
           rebase();
           weights();

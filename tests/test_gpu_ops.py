@@ -501,6 +501,47 @@ def test_attention_one_phase_row_sums_add_weights_in_fp32(dtype, hd):
     assert abs(rel.mean()) <= 0.1 * u
 
 
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("hd", [64, 32])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_attention_one_phase_survives_scores_of_minus_infinity(dtype, hd, mixed):
+    """The first 100 keys score -inf for a query (all of its first key tile), later ones far
+    below and then above zero: its output is the softmax over the finite scores.  mixed: every
+    other query has +inf there instead, so that some lanes of a wave take an exponent base in
+    the first tile (those queries' own outputs are undefined)."""
+    n, H, T, first = 1, 2, 700, 100
+    d, dt = H * hd, tdt(dtype)
+    g = torch.Generator(device="cpu").manual_seed(31)
+    q = torch.randn((n, T, d), generator=g) * 0.1
+    k = torch.randn((n, T, d), generator=g) * 0.1
+    v = torch.randn((n, T, d), generator=g).to(dt)
+    t = torch.arange(T, dtype=torch.float32)
+    score = torch.where(t < 300, torch.full_like(t, -200.0), (t - 300) / 20) + torch.sin(t)
+    for h in range(H):
+        q[:, :, h * hd] = 1.0
+        if mixed:
+            q[:, 1::2, h * hd] = -1.0
+        k[:, :, h * hd] = 0.0
+        k[:, :first, h * hd] = -math.inf
+        q[:, :, h * hd + 1] = 1.0
+        k[:, :, h * hd + 1] = score
+    c = LOG2E / math.sqrt(hd)
+    qk = torch.cat([q.to(dt), k.to(dt)], dim=2)
+    vt = torch.zeros((n, d, K().vt_ld(T)), dtype=dt)
+    vt[:, :, :T] = v.transpose(1, 2)
+    out = torch.full((n, T, d), float("nan"), dtype=dt, device=DEV)
+    K().op_attention(qk.to(DEV), vt.to(DEV), out, n, d, H, [0, T], q_prescaled=True)
+    torch.cuda.synchronize()
+    q64, k64 = qk[0, first:, :d].double().numpy() / c, qk[0, first:, d:].double().numpy()
+    v64 = v[0, first:].double().numpy()
+    got = f64(out[0])[first:]
+    if mixed:
+        odd = np.arange(first, T) % 2 == 1
+        got[odd] = O.causal_attention(q64, k64, v64, [0, T - first], H)[odd]
+    check_heads(got, q64, k64, v64, [0, T - first], H, None, dtype,
+                "attention with infinite scores")
+
+
 def test_attention_dma_base_with_bit31_of_the_low_address_word_set_and_clear():
     """Regression test of a fixed fault.  The ping-pong attention kernel rebuilds each
     wave-uniform 64-bit DMA base from two 32-bit halves; the low half must be widened as
