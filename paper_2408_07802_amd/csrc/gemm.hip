@@ -14,10 +14,11 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // constants are a fit to measured times (fp16 / bf16: 3193 runs over 65 to 17228 rows, widths
 // 256 to 16384, 1 to 8 K splits; fp32: 850 runs): the plan with the least modelled time is on
 // average 1.5% (fp32 2%) slower than the fastest of all plans.
-// A launch takes at least as long as its weights do at the rate the kernel streams them from
-// HBM (128 rows, 4 x 4992 -> 9984 and 4992 columns: 3.5 TB/s in 128 x 128 tiles, 5.0 through
-// the streaming kernel's tiles of 5 blocks of columns, 2.8 to 3.4 through 1 or 2); a little of
-// the modelled time then breaks ties.
+// A launch takes at least as long as its weights do at the rate the kernel streams them into LDS
+// (128 rows, weights from HBM, 4 x 4992 -> 9984 and 4992 columns: 3.5 TB/s in 128 x 128 tiles, 5.0
+// through the streaming kernel's tiles of 5 blocks of columns, 2.8 to 3.4 through 1 or 2; the same
+// 5.0 where two terms stream the weights twice, a W_concat of 4 x 4992 -> 4992 in 80 us); a little
+// of the modelled time then breaks ties.
 struct TileCost {
   double launch, round, slice, slice_nb, load, gelu, stream;   // stream: TB/s
   double us(int64_t tiles, int64_t slots, int64_t slices, int nb, bool with_gelu,
@@ -64,24 +65,29 @@ constexpr int MID_ROWS = 512, MID_ROWS_NARROW = 1536, MID_ROWS_LAST = 2560, MID_
 //             everywhere (64 rows, eight of 2048 -> 8192: 119 and 80)
 //   fp32      four of 4096 -> 1024 at 1 row 24.1 with 8 waves, 19.0 with 16; at 64 rows 48.5, the
 //             streaming kernel 70
-bool skinny_wins(bool f32, int M, int N, int64_t Kall, int batch, int64_t part_elems) {
+bool skinny_wins(bool f32, int M, int N, int64_t Kall, int terms, int batch,
+                 int64_t part_elems) {
   if (M > 64 || batch > 65535) return false;        // (the batch is a grid dimension)
   if (M <= 16 || f32) return true;
-  // 17 to 32 rows: few columns and a reduction that is short or cannot be split
-  return M <= 32 && (int64_t)N * batch <= 4096 && (Kall <= 2048 || part_elems == 0);
+  // 17 to 32 rows: few columns and a reduction that is short (counting the loads of A, which
+  // two terms double) or cannot be split
+  return M <= 32 && (int64_t)N * batch <= 4096 && (Kall * terms <= 2048 || part_elems == 0);
 }
 
-GemmPlan skinny_plan(bool f32, int M, int N, int64_t Kall, int batch, int64_t part_elems,
-                     bool own_sum) {
+GemmPlan skinny_plan(bool f32, int M, int N, int64_t Kall, int terms, int batch,
+                     int64_t part_elems, bool own_sum) {
   const int64_t blocks = ceil_div(N, 16) * batch;   // workgroups of one column block
   GemmPlan p{GemmKind::SKINNY, 1, 1, 4};
   if (f32 && M <= 16) p.waves = 16;
-  else if (f32 || Kall >= 2048 || blocks <= 512) p.waves = 8;
+  else if (f32 || Kall * terms >= 2048 || blocks <= 512) p.waves = 8;
   // two column blocks (each A fragment feeds two MFMAs) once they still fill the chip
-  if (!f32 && M > 1 && blocks >= 1024 && Kall >= 2048) p.nb = 2;
+  if (!f32 && M > 1 && blocks >= 1024 && Kall * terms >= 2048) p.nb = 2;
   // Few column blocks and a long reduction: K splits, as long as every wave keeps a whole batch
-  // of 8 steps.  A batch less per wave saves about 3 us; a launch for the sum costs 4.
-  const int64_t batches = Kall / (f32 ? 16 : 32) / (8 * p.waves);
+  // of 8 loads of A: 8 steps, or 4 steps of two terms.  A batch less per wave saves about 3 us; a
+  // launch for the sum costs 4.  (Two terms, 1 row, with the sum's launch, us in 1 / 2 / 4 / 8
+  // splits: 4 x 1024 -> 1024, 16 steps a wave whole, 11.3 / 9.3 / 7.3 / 7.2; 4 x 768 -> 768, 12
+  // steps, 7.4 / 6.8 / 5.9 / 6.4; 4 x 256 -> 256, 4 steps, 3.4 / 4.6 / 4.4.)
+  const int64_t batches = Kall * terms / (f32 ? 16 : 32) / (8 * p.waves);
   const int64_t sp = std::min<int64_t>(
       {8, 512 / blocks, batches, part_elems / ((int64_t)M * N * batch)});
   if (sp > 1 && (!own_sum || 3 * (batches - batches / sp) > 6)) p.splits = (int)sp;
@@ -90,13 +96,15 @@ GemmPlan skinny_plan(bool f32, int M, int N, int64_t Kall, int batch, int64_t pa
 
 }  // namespace
 
-GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
+GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int terms, int batch,
                    int64_t part_elems, bool own_sum) {
   const bool f32 = dt == DType::F32;
   const int64_t Kall = (int64_t)K * kgroups;
-  if (epi != EPI_BIAS_M && skinny_wins(f32, M, N, Kall, batch, part_elems))
-    return skinny_plan(f32, M, N, Kall, batch, part_elems, own_sum);
-  const int64_t slices = (int64_t)K / (f32 ? 32 : 64) * kgroups;
+  if (epi != EPI_BIAS_M && skinny_wins(f32, M, N, Kall, terms, batch, part_elems))
+    return skinny_plan(f32, M, N, Kall, terms, batch, part_elems, own_sum);
+  // The other kernels walk the groups once per term, and load every weight each time: slices and
+  // streamed bytes count per term.
+  const int64_t slices = (int64_t)K / (f32 ? 32 : 64) * kgroups * terms;
   const int64_t t256 = ceil_div(M, 256) * ceil_div(N, 256) * batch;
   const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128) * batch;
   GemmPlan best{GemmKind::TILE256, 0, 1, 0};
@@ -109,7 +117,8 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batc
   };
   const int64_t plane = (int64_t)M * N * batch;
   const int rows = epi == EPI_BIAS_M ? N : M;
-  const double wmb = (double)(epi == EPI_BIAS_M ? M : N) * (double)Kall * batch * (f32 ? 4e-6 : 2e-6);
+  const double wmb = (double)(epi == EPI_BIAS_M ? M : N) * (double)(Kall * terms) * batch *
+                     (f32 ? 4e-6 : 2e-6);
   for (int sp = 1; sp <= 8; ++sp) {
     // Splits keep at least 8 slices each (2 of the four times longer fp32 ones; a shorter
     // reduction gains under 0.3 us per split); their planes must fit.  A plane costs about
@@ -189,7 +198,7 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
 
 hipError_t launch_gemm(const GemmDesc& g, hipStream_t s) {
   return launch_gemm_planned(
-      g, plan_gemm(g.dt, g.epi, g.M, g.N, g.K, g.kgroups, g.batch, 0, false), s);
+      g, plan_gemm(g.dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, g.batch, 0, false), s);
 }
 
 }  // namespace kraken

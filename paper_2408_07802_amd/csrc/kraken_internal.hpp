@@ -126,11 +126,14 @@ struct GemmPlan {
   int waves;    // SKINNY: waves that share a workgroup's reduction (4, 8; 16 for fp32
                 // up to 16 rows)
 };
-// Plan of a GEMM of type dt.  part_elems: fp32 elements available for K-split partial planes
+// Plan of a GEMM of type dt.  terms: 2 for a two-term operand A (hi and lo: W_concat of 16-bit
+// operands) over kgroups K groups of weights; SKINNY multiplies both terms with one load of a
+// weight (kgroups groups, gA2 != 0), the others walk terms x kgroups groups (gBmod = kgroups).
+// part_elems: fp32 elements available for K-split partial planes
 // (0: no split; only EPI_BIAS_N_RES results can be split).
 // Only results that the caller sums itself (see PartSum) may be given part_elems > 0; own_sum:
 // the sum takes a launch of its own.
-GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int batch,
+GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int terms, int batch,
                    int64_t part_elems, bool own_sum);
 hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStream_t s);
 // The kernels of the plans TILE256 / TILE128, MID and SKINNY (one object file per operand type).

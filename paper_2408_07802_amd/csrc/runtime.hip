@@ -542,13 +542,13 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // together and their planes summed as one, or neither is.
   const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
   const int64_t room = parallel ? m->part_elems / 2 : m->part_elems;
-  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, room, false);
-  GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N, room, false);
+  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, 1, (int)N, room, false);
+  GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, 1, (int)N, room, false);
   const GemmPlan plan_o_whole =
-      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, (int)N, 0, false);
+      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, 1, (int)N, 0, false);
   // the last layer's x has no LayerNorm behind it
   const GemmPlan plan_d_last =
-      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, (int)N, room, true);
+      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, 1, (int)N, room, true);
   const int64_t plane = N * Td;
   PartSum xsum;                       // the previous layer's x, if it is still in planes
   // W_concat's 16-bit operand: x = hi + lo, written by the last FFN-down projection itself
@@ -561,7 +561,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // decode step's cache), where the kernels for few or some hundred rows run it; the tiled
   // kernels of larger prompts take two projections.  (32-bit offsets: all three together may
   // be too large for one.)
-  const GemmPlan plan_qkv = plan_gemm(dt, EPI_QKV, T, (int)dqkv, (int)dp, 1, (int)N, 0, false);
+  const GemmPlan plan_qkv = plan_gemm(dt, EPI_QKV, T, (int)dqkv, (int)dp, 1, 1, (int)N, 0, false);
   const bool merged = (plan_qkv.kind == GemmKind::SKINNY || plan_qkv.kind == GemmKind::MID) &&
                       dqkv * dp * (int64_t)sz(dt) < (1ll << 31);
   QkvOut qkv = {};
@@ -758,14 +758,9 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     // stored rows are wanted.
     GemmDesc g = gemm_base(dt);
     g.epi = EPI_BIAS_N_RES;
-    if (dt != DType::F32) {
-      // 16-bit operands: Y = hi + lo with hi = S(Y), lo = S(Y - hi); 2N groups
-      g.A = hilo;
-      g.kgroups = (int)(2 * N);
-    } else {
-      g.A = m->xbuf;
-      g.kgroups = (int)N;
-    }
+    // 16-bit operands: Y = hi + lo with hi = S(Y), lo = S(Y - hi), two terms of N groups each
+    const int terms = wcat16 ? 2 : 1;
+    g.A = wcat16 ? hilo : m->xbuf;
     g.lda = (int)dp; g.gA = Td;
     g.B = m->WcatT; g.ldb = (int)(N * dp); g.gB = dp; g.gBmod = (int)N;
     g.M = T; g.K = (int)dp;
@@ -775,11 +770,11 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     } else {
       g.C = hidden_out; g.ldc = (int)d; g.N = (int)d;
     }
-    const GemmPlan plan = plan_gemm(dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, m->part_elems, true);
-    if (plan.kind == GemmKind::SKINNY && wcat16) {
-      g.kgroups = (int)N;              // both terms of a sub-layer against one read of its weights
-      g.gA2 = N * Td;
-    }
+    const GemmPlan plan =
+        plan_gemm(dt, g.epi, g.M, g.N, g.K, (int)N, terms, 1, m->part_elems, true);
+    const bool dual = wcat16 && plan.kind == GemmKind::SKINNY;   // both terms in one step
+    g.kgroups = (int)(dual ? N : terms * N);
+    g.gA2 = dual ? N * Td : 0;
     if (plan.splits > 1) {
       PartSum ps;
       ps.part = m->part; ps.splits = plan.splits; ps.plane = (int64_t)T * g.N;

@@ -31,10 +31,10 @@ def _lib():
     return kraken.lib()
 
 
-def plan(dt, epi, M, N, K, kgroups, batch, part, own_sum=False):
-    f = getattr(_lib(), "_ZN6kraken9plan_gemmENS_5DTypeEiiiiiilb")
-    f.argtypes, f.restype = [I] * 7 + [L, ctypes.c_bool], Plan
-    return f(dt, epi, M, N, K, kgroups, batch, part, own_sum)
+def plan(dt, epi, M, N, K, kgroups, batch, part, own_sum=False, terms=1):
+    f = getattr(_lib(), "_ZN6kraken9plan_gemmENS_5DTypeEiiiiiiilb")
+    f.argtypes, f.restype = [I] * 8 + [L, ctypes.c_bool], Plan
+    return f(dt, epi, M, N, K, kgroups, terms, batch, part, own_sum)
 
 
 def test_plans_stay_within_their_limits():
@@ -57,13 +57,29 @@ def test_plans_stay_within_their_limits():
         assert p.splits == 1 or p.splits * M * N * b <= part
 
 
+@pytest.mark.parametrize("dt,terms", [(F32, 1), (F16, 1), (F16, 2)])
+def test_few_row_splits_leave_every_wave_a_batch_of_loads(dt, terms):
+    # the splits of a W_concat (own_sum), in the steps that the kernel really walks: 8 loads of
+    # A for every wave, whichever number of terms a step loads
+    rng, split = random.Random(5), 0
+    for _ in range(3000):
+        M, N, d = rng.choice([1, 2, 7, 16]), rng.choice([1, 2, 4, 8]), 64 * rng.randint(2, 40)
+        p = plan(dt, RES, M, d, d, N, 1, 1 << 26, True, terms=terms)
+        assert p.kind == SKINNY
+        steps = N * d // (16 if dt == F32 else 32)
+        if p.splits > 1:
+            split += 1
+            assert steps * terms // (p.splits * p.waves) >= 8, (M, N, d, p.splits, p.waves)
+    assert split > 100
+
+
 def test_large_prompts_keep_their_rows_independent_of_the_length():
     # the benchmark layer at 4096 and 8192 tokens: whole reductions either way, so a prefix
     # gives the same bits
     for M in (4096, 8192):
         for N, K in ((4096, 2048), (2048, 2048), (8192, 2048), (2048, 8192)):
             assert plan(F16, RES, M, N, K, 1, 8, 1 << 26).splits == 1
-        assert plan(F16, RES, M, 2048, 2048, 16, 1, 1 << 26, True).splits == 1    # W_concat
+        assert plan(F16, RES, M, 2048, 2048, 8, 1, 1 << 26, True, terms=2).splits == 1  # W_concat
 
 
 # (M, N, K, batch, K splits): one row past and short of tiles of 128 and 256, column counts
