@@ -362,10 +362,74 @@ size_t carve_weights(kraken_model* m, void* base) {
   return c.off;
 }
 
-// Most fp32 elements of a model's partial planes.  The largest measured gain of a split that
-// needs nearly as many: W_concat of four sub-layers of width 1280 over 17228 tokens, 457 us
-// whole and 383 us in two planes (44 million elements).
-constexpr size_t PART_MAX_ELEMS = 64u << 20;
+// Projections of a layer whose reduction may be split (forward has the reasons): their plans for
+// T rows, and which of them leave their result as partial planes.  room: fp32 elements that the
+// planes may take.
+struct LayerPlans {
+  GemmPlan o, down;
+  bool part_o, part_down;
+};
+LayerPlans layer_plans(const Dims& D, DType dt, int T, int64_t room, bool last) {
+  // The parallel layer has no kernel that reads h alone: its two projections are split
+  // together and their planes summed as one, or neither is.
+  const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
+  if (parallel) room /= 2;
+  const int dp = (int)D.dp, dq = (int)D.dq, Fp = (int)D.Fp;
+  LayerPlans p;
+  // (the last layer's x has no LayerNorm behind it: a launch of its own sums it)
+  p.down = plan_gemm(dt, EPI_BIAS_N_RES, T, dp, Fp, 1, 1, D.N, room, last);
+  p.part_down = p.down.splits > 1;
+  p.o = plan_gemm(dt, EPI_BIAS_N_RES, T, dp, dq, 1, 1, D.N, room, false);
+  p.part_o = parallel ? p.part_down : p.o.splits > 1;
+  if (!p.part_o) p.o = plan_gemm(dt, EPI_BIAS_N_RES, T, dp, dq, 1, 1, D.N, 0, false);
+  return p;
+}
+
+// Plan of W_concat for T rows and N columns; 16-bit operands are hi + lo, two terms.
+GemmPlan concat_plan(const Dims& D, DType dt, int T, int N, int64_t room) {
+  return plan_gemm(dt, EPI_BIAS_N_RES, T, N, D.dp, D.N, dt == DType::F32 ? 1 : 2, 1, room, true);
+}
+
+// fp32 elements that the partial planes of these plans take for T rows.
+int64_t layer_planes(const Dims& D, const LayerPlans& p, int T) {
+  const int64_t plane = (int64_t)D.N * T * D.dp;
+  if (D.arch == KRAKEN_ARCH_PARALLEL) return p.part_down ? (p.o.splits + p.down.splits) * plane : 0;
+  return std::max(p.part_o ? p.o.splits : 0, p.part_down ? p.down.splits : 0) * plane;
+}
+int64_t concat_planes(const GemmPlan& p, int T, int N) {
+  return p.splits > 1 ? (int64_t)p.splits * T * N : 0;
+}
+
+// Room that plans may count on for their planes in a model of Tmax tokens: 8 of the widest
+// result, and at most 256 MB of memory.  A model allocates what its plans ask for within it: 192
+// MB for 8 sub-layers of width 2048 and 8192 tokens, 146 MB for 4 of 1280 and 18580 tokens, 32 MB
+// for 4 of 1024 and 2048 tokens.
+int64_t plane_room(const Dims& D, int Tmax) {
+  return std::min<int64_t>(8 * (int64_t)D.N * Tmax * D.dp, 64 << 20);
+}
+
+// Most elements that the planes of any pass over T rows take, in a model of Tmax tokens.
+int64_t planes_at(const Dims& D, DType dt, int T, int Tmax) {
+  const int64_t room = plane_room(D, Tmax);
+  int64_t n = layer_planes(D, layer_plans(D, dt, T, room, true), T);
+  if (D.L > 1) n = std::max(n, layer_planes(D, layer_plans(D, dt, T, room, false), T));
+  if (D.arch == KRAKEN_ARCH_KRAKEN)
+    for (int N : {D.d, D.dp})
+      n = std::max(n, concat_planes(concat_plan(D, dt, T, N, room), T, N));
+  return n;
+}
+
+// The same over all T up to Tmax.  Past 128 rows plans are made once per 16: within such a block
+// every kernel has the same tiles, and the cost and limit of the planes only grow with T, so the
+// first row has the most splits.
+int64_t planes_upto(const Dims& D, DType dt, int Tmax) {
+  const int64_t room = plane_room(D, Tmax);
+  int64_t n = 0;
+  for (int T = 1; T <= std::min(Tmax, 128); ++T) n = std::max(n, planes_at(D, dt, T, Tmax));
+  for (int T = 129; T <= Tmax && 2 * (int64_t)T * D.d <= room; T += 16)
+    n = std::max(n, planes_at(D, dt, T, Tmax) / T * std::min(T + 15, Tmax));
+  return std::min(n, room);
+}
 
 size_t carve_workspace(kraken_model* m, void* base) {
   Carver c(base);
@@ -383,8 +447,7 @@ size_t carve_workspace(kraken_model* m, void* base) {
   m->act = c.take(N * T * dp * es);
   m->qk = c.take(N * T * (dq + dkv) * es);
   m->o = c.take(N * T * std::max(dq, dkv) * es);
-  // Planes of K-split GEMMs (see plan_gemm): up to 8 of the widest result, at most 256 MB
-  m->part_elems = (int64_t)std::min<size_t>(8 * N * T * dp, PART_MAX_ELEMS);
+  m->part_elems = planes_upto(D, m->dt, m->Tmax);
   m->part = (float*)c.take(m->part_elems * sizeof(float));
   // vt and g stay adjacent and last: a decode step keeps its attention partials there
   m->vt = c.take(N * dkv * (size_t)vt_ld(m->Tmax) * es);
@@ -538,23 +601,19 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   // The output and FFN-down projections have few columns and a long reduction; where that
   // leaves CUs idle their reduction is split (plan_gemm), and the kernel that reads the result
   // sums the planes: LN2 for h, the next LN1 (or, after the last layer, launch_finish) for x.
-  // The parallel layer has no kernel that reads h alone: its two projections are split
-  // together and their planes summed as one, or neither is.
   const bool parallel = D.arch == KRAKEN_ARCH_PARALLEL;
-  const int64_t room = parallel ? m->part_elems / 2 : m->part_elems;
-  GemmPlan plan_o = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, 1, (int)N, room, false);
-  GemmPlan plan_d = plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, 1, (int)N, room, false);
-  const GemmPlan plan_o_whole =
-      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)dq, 1, 1, (int)N, 0, false);
-  // the last layer's x has no LayerNorm behind it
-  const GemmPlan plan_d_last =
-      plan_gemm(dt, EPI_BIAS_N_RES, T, (int)dp, (int)Fp, 1, 1, (int)N, room, true);
+  const int64_t room = plane_room(D, m->Tmax);
+  const LayerPlans plan_inner = layer_plans(D, dt, T, room, false);
+  const LayerPlans plan_last = layer_plans(D, dt, T, room, true);
+  if (layer_planes(D, plan_last, T) > m->part_elems ||
+      (m->L > 1 && layer_planes(D, plan_inner, T) > m->part_elems))
+    return fail(KRAKEN_ERR_STATE, "partial planes exceed the workspace");
   const int64_t plane = N * Td;
   PartSum xsum;                       // the previous layer's x, if it is still in planes
   // W_concat's 16-bit operand: x = hi + lo, written by the last FFN-down projection itself
   // where it is not split and nobody wants x
   const bool wcat16 = D.arch == KRAKEN_ARCH_KRAKEN && dt != DType::F32;
-  const bool part_last = plan_d_last.splits > 1;
+  const bool part_last = plan_last.part_down;
   const bool hilo_epi = wcat16 && !part_last && !sub_out;
 
   // Q, K and V in one projection, each column stored where it is read (Q | K rows and V^T, or a
@@ -574,10 +633,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   for (int j = 0; j < m->L; ++j) {
     const LayerW& w = m->layers[j];
     const bool last = j + 1 == m->L;
-    const GemmPlan& plan_dj = last ? plan_d_last : plan_d;
-    const bool part_d = plan_dj.splits > 1;
-    const bool part_o = parallel ? part_d : plan_o.splits > 1;
-    const GemmPlan& plan_oj = part_o ? plan_o : plan_o_whole;
+    const LayerPlans& plan = last ? plan_last : plan_inner;
     const float* xin = j == 0 ? X32 : m->xbuf;   // sub-layer inputs x_i
     const int64_t xs = j == 0 ? 0 : Td;           // first layer: one shared input
     char* cache_j = kv ? kv->cache + (size_t)j * kv->layer_bytes : nullptr;
@@ -658,14 +714,14 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       g.bias = w.bo; g.sBias = dp;
       g.R = xin; g.sR = xs;
       g.M = T; g.N = (int)dp; g.K = (int)dq; g.batch = (int)N;
-      if (part_o) {
+      if (plan.part_o) {
         g.epi = EPI_PART;
         g.C = m->part;
-        g.splits = plan_oj.splits; g.sPlane = plane;
-        hsum.part = m->part; hsum.splits = plan_oj.splits; hsum.plane = plane;
+        g.splits = plan.o.splits; g.sPlane = plane;
+        hsum.part = m->part; hsum.splits = plan.o.splits; hsum.plane = plane;
         hsum.bias = w.bo; hsum.res = xin; hsum.res_stride = xs; hsum.out = m->hbuf;
       }
-      RUN(KRAKEN_K_GEMM_O, launch_gemm_planned(g, plan_oj, s), "output projection");
+      RUN(KRAKEN_K_GEMM_O, launch_gemm_planned(g, plan.o, s), "output projection");
     }
     // The FFN's LayerNorm: Kraken reads h + y with y the combine (Algorithm 1); the
     // GPT-like layer reads h; the parallel layer's FFN takes the LN1 output still in act.
@@ -699,18 +755,18 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
       g.bias = w.b2; g.sBias = dp;
       g.R = m->hbuf; g.sR = Td;
       g.M = T; g.N = (int)dp; g.K = (int)Fp; g.batch = (int)N;
-      if (part_d) {
+      if (plan.part_down) {
         g.epi = EPI_PART;
-        g.splits = plan_dj.splits; g.sPlane = plane;
+        g.splits = plan.down.splits; g.sPlane = plane;
         if (parallel) {
           // x = xin + O planes + FFN planes + bo + b2
-          g.C = m->part + plan_oj.splits * plane;
+          g.C = m->part + plan.o.splits * plane;
           xsum = hsum;
-          xsum.splits += plan_dj.splits;
+          xsum.splits += plan.down.splits;
           xsum.bias2 = w.b2;
         } else {
           g.C = m->part;
-          xsum.part = m->part; xsum.splits = plan_dj.splits; xsum.plane = plane;
+          xsum.part = m->part; xsum.splits = plan.down.splits; xsum.plane = plane;
           xsum.bias = w.b2; xsum.res = m->hbuf; xsum.res_stride = Td;
         }
         xsum.out = m->xbuf;
@@ -719,7 +775,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
         g.sPlane = N * Td;
         g.ovf = ovf;
       }
-      RUN(KRAKEN_K_GEMM_DOWN, launch_gemm_planned(g, plan_dj, s), "FFN down");
+      RUN(KRAKEN_K_GEMM_DOWN, launch_gemm_planned(g, plan.down, s), "FFN down");
     }
   }
 
@@ -759,7 +815,6 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     GemmDesc g = gemm_base(dt);
     g.epi = EPI_BIAS_N_RES;
     // 16-bit operands: Y = hi + lo with hi = S(Y), lo = S(Y - hi), two terms of N groups each
-    const int terms = wcat16 ? 2 : 1;
     g.A = wcat16 ? hilo : m->xbuf;
     g.lda = (int)dp; g.gA = Td;
     g.B = m->WcatT; g.ldb = (int)(N * dp); g.gB = dp; g.gBmod = (int)N;
@@ -770,10 +825,11 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     } else {
       g.C = hidden_out; g.ldc = (int)d; g.N = (int)d;
     }
-    const GemmPlan plan =
-        plan_gemm(dt, g.epi, g.M, g.N, g.K, (int)N, terms, 1, m->part_elems, true);
+    const GemmPlan plan = concat_plan(D, dt, T, g.N, room);
+    if (concat_planes(plan, T, g.N) > m->part_elems)
+      return fail(KRAKEN_ERR_STATE, "partial planes exceed the workspace");
     const bool dual = wcat16 && plan.kind == GemmKind::SKINNY;   // both terms in one step
-    g.kgroups = (int)(dual ? N : terms * N);
+    g.kgroups = (int)(wcat16 && !dual ? 2 * N : N);
     g.gA2 = dual ? N * Td : 0;
     if (plan.splits > 1) {
       PartSum ps;
@@ -820,6 +876,18 @@ kraken_status check_cache(const kraken_model* m, const void* cache, int32_t max_
 }
 
 }  // namespace
+
+namespace kraken {
+
+// fp32 elements of partial planes: what a pass over T rows takes, or, for T = 0, what a model of
+// this configuration allocates.
+int64_t partial_plane_elems(const kraken_config* c, int T) {
+  const Dims D = dims_of(c);
+  const DType dt = (DType)(c->compute == KRAKEN_COMPUTE_STORAGE ? c->dtype : c->compute - 1);
+  return T > 0 ? planes_at(D, dt, T, c->max_tokens) : planes_upto(D, dt, c->max_tokens);
+}
+
+}  // namespace kraken
 
 extern "C" {
 

@@ -82,6 +82,37 @@ def test_large_prompts_keep_their_rows_independent_of_the_length():
         assert plan(F16, RES, M, 2048, 2048, 8, 1, 1 << 26, True, terms=2).splits == 1  # W_concat
 
 
+def test_models_allocate_the_planes_that_their_plans_ask_for():
+    from paper_2408_07802_amd import kraken
+    f = getattr(_lib(), "_ZN6kraken19partial_plane_elemsEPK13kraken_configi")
+    f.argtypes, f.restype = [P, I], L
+
+    def elems(cfg, T):                  # of a pass over T rows; T = 0: of the model
+        c = cfg.c_struct()
+        return f(ctypes.addressof(c), T)
+
+    rng, split = random.Random(7), 0
+    for _ in range(300):
+        arch = rng.choice(["kraken", "gpt", "parallel"])
+        hd, heads = rng.choice([32, 64, 128]), 2 * rng.randint(1, 16)
+        cfg = kraken.Config(
+            n_sub=rng.choice([1, 2, 4, 8]) if arch == "kraken" else 1, n_layers=rng.choice([1, 2]),
+            d_model=hd * heads - rng.choice([0, 0, 20]), n_heads=heads, head_dim=hd,
+            d_ff=hd * heads * rng.choice([1, 2, 4]), arch=arch, dtype=rng.choice(["f16", "f32"]),
+            max_tokens=int(math.exp(rng.uniform(0, math.log(20000)))))
+        room, T = elems(cfg, 0), cfg.max_tokens
+        assert room <= 64 << 20
+        need = [elems(cfg, t) for t in [T] + [rng.randint(1, T) for _ in range(40)]]
+        assert max(need) <= room, cfg
+        split += max(need) > 0
+    assert split > 100
+    # a small model does not pay for planes that none of its plans can have (8 planes of the
+    # widest result would be 256 MB)
+    small = kraken.Config(n_sub=4, n_layers=1, d_model=1024, n_heads=16, d_ff=4096,
+                          max_tokens=2048, dtype="bf16", compute="f16")
+    assert elems(small, 0) * 4 <= 32 << 20
+
+
 # (M, N, K, batch, K splits): one row past and short of tiles of 128 and 256, column counts
 # that are no multiple of a tile or of 4, splits of unequal length, a single slice
 SHAPES = [(65, 96, 64, 1, 1), (127, 130, 192, 2, 3), (128, 160, 128, 1, 2), (129, 257, 320, 2, 5),
