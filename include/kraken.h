@@ -216,6 +216,9 @@ kraken_status kraken_load_weights(kraken_model* m, const void* blob, size_t nbyt
  *               outputs Y_i before W_concat.
  * Outputs are fp32 whatever the storage dtype (the residual stream and all
  * accumulation are fp32).  Outputs must not overlap the input or each other.
+ * A call repeated on the same inputs gives the same bits.  The order of the fp32
+ * sums is chosen by the call's number of rows T (kernels, tiles and K splits), so
+ * a token's outputs in calls of different T agree up to rounding, not bit for bit.
  * The call enqueues the whole pass on `stream` and returns; it keeps no
  * pointer to caller memory.  One prefill at a time per model: concurrent
  * calls on one model must be serialised by the caller (e.g. one stream).

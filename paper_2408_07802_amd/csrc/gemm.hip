@@ -124,9 +124,14 @@ GemmPlan plan_gemm(DType dt, int epi, int M, int N, int K, int kgroups, int term
     // reduction gains under 0.3 us per split); their planes must fit.  A plane costs about
     // 0.1 us per MB to write and 0.2 us per MB to read in the kernel that sums them, which
     // without a split would read one as well, unless it is launched for the sum alone (4 us,
-    // and its result and residual pass through it too).  A launch for the sum alone is not spent
-    // where 128 x 128 tiles fill the chip: W_concat then reduces in one order from some thousand
-    // rows on, and a prefix of a prompt has the bits of the whole.
+    // and its result and residual pass through it too).  A sum with a launch of its own (W_concat,
+    // the last FFN-down) stays whole from 512 tiles of 128 x 128 on: W_concat from 3969 rows at
+    // width 2048, 6529 at 1280, 8065 at 1024.  That is not for speed (17228 rows of four sub-layers
+    // of width 1280: 457 us whole, 383 in two planes) but keeps the outputs of the widest long
+    // prompts in one order: rows 0 .. 4095 of 8192 are those of a 4096-token prompt to the last
+    // bits at width 2048.  It is no rule for every shape: below the limit, and for the other
+    // projections at any number of rows (GPT-like, width 2048, FFN-down: two planes at 8193 to 12288
+    // rows), the order of a sum, and so its last bits, depend on the number of rows.
     if (sp > 1 && (sp * plane > part_elems || slices < (f32 ? 2 : 8) * sp ||
                    (own_sum && t128 >= 512)))
       break;

@@ -73,13 +73,25 @@ def test_few_row_splits_leave_every_wave_a_batch_of_loads(dt, terms):
     assert split > 100
 
 
-def test_large_prompts_keep_their_rows_independent_of_the_length():
-    # the benchmark layer at 4096 and 8192 tokens: whole reductions either way, so a prefix
-    # gives the same bits
+def test_benchmark_layer_is_whole_at_4096_and_8192_rows():
+    # the benchmark layer at these two lengths alone: whole reductions, so the longer prompt's
+    # rows have the bits of the shorter one's (which a GPU test compares)
     for M in (4096, 8192):
         for N, K in ((4096, 2048), (2048, 2048), (8192, 2048), (2048, 8192)):
             assert plan(F16, RES, M, N, K, 1, 8, 1 << 26).splits == 1
         assert plan(F16, RES, M, 2048, 2048, 8, 1, 1 << 26, True, terms=2).splits == 1  # W_concat
+
+
+def test_sums_with_a_launch_of_their_own_stay_whole_from_512_tiles():
+    # W_concat (N sub-layers of width d), from the row count on that the planner's comment names
+    for N, d, rows in ((8, 2048, 3969), (4, 1280, 6529), (4, 1024, 8065)):
+        for M in [rows, rows + 1] + [random.Random(d).randint(rows, 20000) for _ in range(50)]:
+            assert plan(F16, RES, M, d, d, N, 1, 1 << 26, True, terms=2).splits == 1, (M, d)
+    # and no promise below it, nor for a plane that the next kernel sums
+    assert plan(F16, RES, 4096, 1280, 1280, 4, 1, 1 << 26, True, terms=2).splits == 3
+    assert plan(F16, RES, 4096, 1024, 1024, 4, 1, 1 << 26, True, terms=2).splits == 4
+    assert plan(F16, RES, 3584, 2048, 2048, 8, 1, 1 << 26, True, terms=2).splits > 1
+    assert plan(F16, RES, 9000, 2048, 8192, 1, 1, 1 << 26).splits == 2
 
 
 def test_models_allocate_the_planes_that_their_plans_ask_for():
