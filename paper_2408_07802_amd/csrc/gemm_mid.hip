@@ -254,7 +254,10 @@ __global__ __launch_bounds__(512, 1) void gemm_mid_kernel(GemmParams p, QkvArg<E
   using OutT = typename std::conditional<epi_f32<EPI>, float, S>::type;
   OutT* Cz = static_cast<OutT*>(p.C) + z * p.sC + (EPI == EPI_PART ? sp * p.sPlane : 0);
   const float* Rz = epi_res<EPI> && p.R ? p.R + z * p.sR : nullptr;
-  const bool vec_ok = (p.ldc & 3) == 0;
+  // (results and residuals of callers, such as logits, need not be aligned to four elements)
+  const bool vec_ok = (p.ldc & 3) == 0 &&
+                      (reinterpret_cast<uintptr_t>(Cz) & (4 * sizeof(OutT) - 1)) == 0 &&
+                      (reinterpret_cast<uintptr_t>(Rz) & 15) == 0;
   float amax = 0.f;
 #pragma unroll 4
   for (int q = 0; q < 2 * NB; ++q) {

@@ -574,6 +574,10 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     if (e != hipSuccess) return hip_fail(e, what); \
   } while (0)
 
+  // hidden_out is an fp32 array of the caller's; the kernels that write it store 16 bytes at a
+  // time, so rows for one that is not aligned to that pass through the workspace.
+  const bool out_ok = reinterpret_cast<uintptr_t>(hidden_out) % 16 == 0;
+
   const float* X32 = m->X32;
   if (hidden_in) {
     if (m->st == DType::F32 && d == dp) {
@@ -791,7 +795,8 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     }
     ps.out = !part_last || (wcat16 && !sub_out) ? nullptr : m->xbuf;
     int64_t ld = dp;
-    if (D.arch != KRAKEN_ARCH_KRAKEN && hidden_out && !sub_out && !final_rows && d == dp) {
+    if (D.arch != KRAKEN_ARCH_KRAKEN && hidden_out && out_ok && !sub_out && !final_rows &&
+        d == dp) {
       ps.out = hidden_out;
       ld = d;
       out_done = true;
@@ -811,7 +816,8 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
   if (D.arch == KRAKEN_ARCH_KRAKEN) {
     // out = [Y_1 | ... | Y_N] W_concat, K split into N groups of dp (one per sub-layer).
     // Into the caller's [T][d] directly, or into X32 (free after the first layer) when the
-    // stored rows are wanted.
+    // stored rows are wanted or hidden_out is not aligned.
+    const bool stored_rows = final_rows || !out_ok;
     GemmDesc g = gemm_base(dt);
     g.epi = EPI_BIAS_N_RES;
     // 16-bit operands: Y = hi + lo with hi = S(Y), lo = S(Y - hi), two terms of N groups each
@@ -819,7 +825,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     g.lda = (int)dp; g.gA = Td;
     g.B = m->WcatT; g.ldb = (int)(N * dp); g.gB = dp; g.gBmod = (int)N;
     g.M = T; g.K = (int)dp;
-    if (final_rows) {
+    if (stored_rows) {
       g.C = m->X32; g.ldc = (int)dp; g.N = (int)dp;
       fin = m->X32;
     } else {
@@ -845,7 +851,7 @@ kraken_status forward(kraken_model* m, const void* hidden_in, int T, const int32
     } else {
       RUN(KRAKEN_K_CONCAT, launch_gemm_planned(g, plan, s), "W_concat");
     }
-    if (final_rows && hidden_out)
+    if (stored_rows && hidden_out)
       RUN(KRAKEN_K_OTHER,
           hipMemcpy2DAsync(hidden_out, d * sizeof(float), fin, dp * sizeof(float),
                            d * sizeof(float), T, hipMemcpyDeviceToDevice, s),

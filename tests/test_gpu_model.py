@@ -241,6 +241,63 @@ def test_forward_tokens_rejects_bad_ids_and_lengths():
     plain.close()
 
 
+# ----------------------------------------------------- buffers aligned to their elements alone
+
+def offset_by_one(shape, dtype, fill):
+    """A contiguous tensor one element past an aligned address, with the elements around it."""
+    n = int(np.prod(shape))
+    whole = torch.full((n + 2,), fill, dtype=dtype, device=DEV)
+    return whole, whole[1:n + 1].view(shape)
+
+
+@pytest.mark.parametrize("arch", ["kraken", "gpt", "parallel"])
+@pytest.mark.parametrize("d,dtype", [(1024, "bf16"), (1000, "bf16"), (1024, "f32")])
+def test_buffers_need_no_alignment_beyond_their_elements(arch, d, dtype):
+    """Input and output one element past an aligned address, at row counts of each kind of
+    kernel, where the last FFN-down or W_concat leaves planes that a launch of its own sums (into
+    hidden_out, for the GPT-like and parallel stacks): the bits of the aligned call, and nothing
+    written beside the rows.  (d = 1000 is stored 1024 wide; W_concat's plan for the stored rows
+    may add in another order.)"""
+    w = small(f"align-{arch}", n_sub=4 if arch == "kraken" else 1, n_layers=1, d_model=d, n_heads=8,
+              head_size=128, d_ff=4096, dtype=dtype, compute="f16" if dtype == "bf16" else "storage",
+              arch=arch)
+    model = build_model(w, 300)
+    for T in (3, 40, 130, 300):
+        X = synth.gen_hidden(w, T, 1, DEV)
+        ref, _ = model.prefill(X, [0, T])
+        if dtype == "bf16":                # (an fp32 input is read where it is, in whole rows)
+            _, Xu = offset_by_one(X.shape, X.dtype, 0)
+            Xu.copy_(X)
+        else:
+            Xu = X
+        whole, out = offset_by_one((T, d), torch.float32, 7.0)
+        model.poison_workspace()
+        model.prefill(Xu, [0, T], out=out)
+        model.sync()
+        say(f"[alignment] {arch} d={d} {dtype} T={T}")
+        assert whole[0] == 7.0 and whole[-1] == 7.0
+        if d % 64 == 0:
+            assert torch.equal(out, ref)
+        else:
+            assert rel_err(f64(out), f64(ref)) <= 1e-5
+    model.close()
+
+
+def test_logits_need_no_alignment():
+    # 40 and 100 sequences: the streaming kernel's rows, a vocabulary of whole groups of four
+    w = small("align-tok", n_sub=1, n_layers=1, d_model=256, n_heads=2, d_ff=512, compute="f16",
+              arch="gpt", vocab=6000, max_positions=8)
+    model = build_model(w, 100)
+    for B in (40, 100):
+        ids, cu = synth.gen_tokens(w, B, 3), list(range(B + 1))
+        ref, _ = model.forward_tokens(ids, cu)
+        whole, logits = offset_by_one((B, w.vocab), torch.float32, 7.0)
+        model.forward_tokens(ids, cu, logits=logits)
+        model.sync()
+        assert whole[0] == 7.0 and whole[-1] == 7.0 and torch.equal(logits, ref)
+    model.close()
+
+
 # ------------------------------------------ the paper's engine shapes (Section 4.3), full depth
 
 ENGINE_CASES = [(m, a) for m in ("1.3b", "6.7b", "13b") for a in ("kraken4", "kraken8")] + \
