@@ -202,6 +202,7 @@ hipError_t launch_gemm_planned(const GemmDesc& g, const GemmPlan& plan, hipStrea
 }
 
 hipError_t launch_gemm(const GemmDesc& g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.kgroups <= 0) return hipSuccess;   // no plan
   return launch_gemm_planned(
       g, plan_gemm(g.dt, g.epi, g.M, g.N, g.K, g.kgroups, 1, g.batch, 0, false), s);
 }

@@ -94,6 +94,19 @@ def test_sums_with_a_launch_of_their_own_stay_whole_from_512_tiles():
     assert plan(F16, RES, 9000, 2048, 8192, 1, 1, 1 << 26).splits == 2
 
 
+@pytest.mark.parametrize("empty", ["M", "N", "batch", "kgroups"])
+def test_an_empty_product_needs_no_plan(empty):
+    # (the planner divides by tile counts; nothing is launched)
+    f = getattr(_lib(), "_ZN6kraken11launch_gemmERKNS_8GemmDescEP12ihipStream_t")
+    f.restype = I
+    for dt in (F32, F16):
+        for M in (8, 100):
+            d = Desc(dt=dt, epi=BIAS_N, M=M, N=64, K=64, lda=64, ldb=64, ldc=64, batch=1, kgroups=1,
+                     gBmod=1)
+            setattr(d, empty, 0)
+            assert f(ctypes.byref(d), P(None)) == 0
+
+
 def test_models_allocate_the_planes_that_their_plans_ask_for():
     from paper_2408_07802_amd import kraken
     f = getattr(_lib(), "_ZN6kraken19partial_plane_elemsEPK13kraken_configi")
