@@ -230,24 +230,23 @@ hipError_t launch_skinny(const GemmDesc& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename S, int MB>
-hipError_t launch_mb(const GemmDesc& g, int tw, int nw, hipStream_t s) {
-  if constexpr (MB == 1 && sizeof(S) == 4) {
-    if (nw == 16)
-      return tw == 2 ? launch_skinny<S, 1, 2, 16>(g, s)
-                     : launch_skinny<S, 1, 1, 16>(g, s);
-  }
-  if (nw == 8) return tw == 2 ? launch_skinny<S, MB, 2, 8>(g, s) : launch_skinny<S, MB, 1, 8>(g, s);
-  return tw == 2 ? launch_skinny<S, MB, 2, 4>(g, s) : launch_skinny<S, MB, 1, 4>(g, s);
-}
-
 }  // namespace
 
+// The forms that skinny_plan chooses, no others: 16-bit operands up to 32 rows, fp32 up to 64.
 template <>
 hipError_t launch_gemm_skinny<KRAKEN_T>(const GemmDesc& g, int tw, int nw, hipStream_t s) {
-  if (g.M <= 16) return launch_mb<KRAKEN_T, 1>(g, tw, nw, s);
-  if (g.M <= 32) return launch_mb<KRAKEN_T, 2>(g, tw, nw, s);
-  return launch_mb<KRAKEN_T, 4>(g, tw, nw, s);
+  using S = KRAKEN_T;
+  if constexpr (sizeof(S) == 2) {
+    if (g.M <= 16 && tw == 1 && nw == 4) return launch_skinny<S, 1, 1, 4>(g, s);
+    if (g.M <= 16 && tw == 1 && nw == 8) return launch_skinny<S, 1, 1, 8>(g, s);
+    if (g.M <= 16 && tw == 2 && nw == 8) return launch_skinny<S, 1, 2, 8>(g, s);
+    if (g.M > 16 && g.M <= 32 && tw == 1 && nw == 8) return launch_skinny<S, 2, 1, 8>(g, s);
+  } else {
+    if (g.M <= 16 && tw == 1 && nw == 16) return launch_skinny<S, 1, 1, 16>(g, s);
+    if (g.M > 16 && g.M <= 32 && tw == 1 && nw == 8) return launch_skinny<S, 2, 1, 8>(g, s);
+    if (g.M > 32 && g.M <= 64 && tw == 1 && nw == 8) return launch_skinny<S, 4, 1, 8>(g, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace kraken

@@ -123,8 +123,8 @@ struct GemmPlan {
   int nb;       // MID: 32-column blocks per tile; SKINNY: 16-column blocks per workgroup (1, 2);
                 // TILE128: 2 for tiles of 64 columns (16-bit operands), else 0
   int splits;   // K splits
-  int waves;    // SKINNY: waves that share a workgroup's reduction (4, 8; 16 for fp32
-                // up to 16 rows)
+  int waves;    // SKINNY: waves that share a workgroup's reduction (fp32 up to 16 rows: 16, else
+                // 8, or 4 with 16-bit operands)
 };
 // Plan of a GEMM of type dt.  terms: 2 for a two-term operand A (hi and lo: W_concat of 16-bit
 // operands) over kgroups K groups of weights; SKINNY multiplies both terms with one load of a
