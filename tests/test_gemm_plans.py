@@ -3,13 +3,15 @@ forced at the edges of its tiles (GPU, against fp64 products of the same operand
 
 import ctypes
 import math
+import os
 import random
+import re
 
 import pytest
 import torch
 
 F32, BF16, F16 = 0, 1, 2
-BIAS_N, GELU, RES, BIAS_M, HILO, PART = range(6)
+BIAS_N, GELU, RES, BIAS_M, HILO, PART, QKV = range(7)
 TILE256, TILE128, MID, SKINNY = range(4)
 P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
 
@@ -20,6 +22,11 @@ class Desc(ctypes.Structure):       # kraken::GemmDesc
                 ("sB", L), ("sC", L), ("sR", L), ("sBias", L), ("batch", I), ("kgroups", I),
                 ("gA", L), ("gB", L), ("gBmod", I), ("splits", I), ("sPlane", L),
                 ("gA2", L), ("qkv", P), ("ovf", P)]
+
+
+class Qkv(ctypes.Structure):        # kraken::QkvOut
+    _fields_ = [("vt", P), ("svt", L), ("cache", P), ("ldv", I), ("dq", I), ("dkv", I), ("hd", I),
+                ("Hkv", I), ("max_seqs", I), ("cap", I), ("lens", I * 256)]
 
 
 class Plan(ctypes.Structure):       # kraken::GemmPlan
@@ -35,6 +42,25 @@ def plan(dt, epi, M, N, K, kgroups, batch, part, own_sum=False, terms=1):
     f = getattr(_lib(), "_ZN6kraken9plan_gemmENS_5DTypeEiiiiiiilb")
     f.argtypes, f.restype = [I] * 8 + [L, ctypes.c_bool], Plan
     return f(dt, epi, M, N, K, kgroups, terms, batch, part, own_sum)
+
+
+@pytest.mark.parametrize("name,mirror", [("GemmDesc", Desc), ("QkvOut", Qkv), ("GemmPlan", Plan)])
+def test_structs_mirror_the_header(name, mirror):
+    import paper_2408_07802_amd as pkg
+    with open(os.path.join(os.path.dirname(pkg.__file__), "csrc", "kraken_internal.hpp")) as f:
+        body = re.search(r"struct %s \{(.*?)\n\};" % name, f.read(), re.S).group(1)
+    fields = []
+    for decl in re.sub(r"//.*", "", body).replace("\n", " ").split(";"):
+        if not decl.strip():
+            continue
+        words = re.match(r"\s*((?:const )?\w+)\s*(.*)", decl)
+        for item in words.group(2).split(","):
+            word = re.match(r"\s*(\**)\s*(\w+)\s*(?:\[(\d+)\])?\s*$", item)
+            pointer = "*" in words.group(2)
+            t = P if pointer else L if words.group(1) == "int64_t" else I
+            fields.append((word.group(2), t * int(word.group(3)) if word.group(3) else t))
+    assert [n for n, _ in fields] == [n for n, _ in mirror._fields_]
+    assert [ctypes.sizeof(t) for _, t in fields] == [ctypes.sizeof(t) for _, t in mirror._fields_]
 
 
 def few_row_forms(dt, M):
@@ -160,10 +186,100 @@ def test_models_allocate_the_planes_that_their_plans_ask_for():
     assert elems(small, 0) * 4 <= 32 << 20
 
 
+# ------------------------------------------------------------------ every kernel, forced (GPU)
+#
+# Operands and results are laid out as a model's: K groups of A one block of rows after the
+# other, K groups of B side by side in a row and used in turn (gBmod of them), results with row
+# strides above N.  Everything around the results holds MARK and must keep it.
+
+TORCH = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}
+UNIT = {torch.float32: 0.0, torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}
+MARK = -768.0                 # exact in every type
+
+
+def launch(d, kind, nb, waves=0):
+    f = getattr(_lib(), "_ZN6kraken19launch_gemm_plannedERKNS_8GemmDescERKNS_8GemmPlanEP12ihipStream_t")
+    f.restype = I
+    rc = f(ctypes.byref(d), ctypes.byref(Plan(kind, nb, d.splits, waves)),
+           P(torch.cuda.current_stream().cuda_stream or None))
+    torch.cuda.synchronize()
+    return rc
+
+
+def check(got, ref, unit, k, sums, what):
+    """Every element within its bound: half a unit of the stored type (unit; two terms of a 16-bit
+    type: that of both, and the smallest step of the second), and the rounding of fp32 sums of k
+    products.  A partial sum is of the size of sums, each addition rounds it by up to 2^-24, and the
+    roundings are independent: sqrt(k) of them in the mean, 32 times that for the largest of 10^6
+    elements and partial sums above that size.  The norm is held to the same without the 32."""
+    err = (got.double() - ref).abs()
+    add = math.sqrt(k) * 2.0 ** -24 * float(sums.pow(2).mean().sqrt())
+    bound = unit * ref.abs() + 32 * add + 2.0 ** -24
+    assert bool((err <= bound).all()), (what, float((err / bound).max()))
+    assert float(err.pow(2).mean().sqrt()) <= \
+        0.75 * unit * float(ref.pow(2).mean().sqrt()) + 4 * add + 2.0 ** -24, what
+
+
+class Product:
+    """One GEMM: operands, its fp64 result, and a descriptor without C."""
+
+    def __init__(self, dt, epi, M, N, K, batch, groups=1, gmod=1, pad=4, dual=False, scale=1.0):
+        self.dt, self.epi, self.M, self.N, self.batch, self.groups = dt, epi, M, N, batch, groups
+        S = TORCH[dt]
+        g = torch.Generator(device="cuda").manual_seed(M + N + K + groups)
+
+        def rand(*shape):
+            return torch.randn(shape, generator=g, device="cuda")
+
+        terms = 2 if dual else 1
+        self.A = rand(terms, groups, batch, M, K).to(S)
+        self.B = (rand(batch, N, gmod, K) / math.sqrt(K * groups * terms)).to(S)
+        self.bias = rand(batch, M if epi == BIAS_M else N)
+        self.ldc, self.rows = N + pad, M + 1
+        self.R = rand(batch, self.rows, self.ldc)
+        a64 = self.A.double().sum(0) if dual else self.A[0].double()
+        b64 = self.B.double()
+        self.sums = torch.stack([sum(a64[t, z] @ b64[z, :, t % gmod].T for t in range(groups))
+                                 for z in range(batch)])
+        ref = self.sums
+        if epi != PART:
+            ref = ref + (self.bias.double()[:, :, None] if epi == BIAS_M
+                         else self.bias.double()[:, None])
+        if epi == GELU:
+            ref = torch.nn.functional.gelu(ref)
+        if epi in (RES, HILO):
+            ref = ref + self.R[:, :M, :N].double()
+        self.ref, self.k = ref, K * groups * terms
+        self.out = torch.float32 if epi in (RES, PART) else S
+        size = self.rows * self.ldc
+        self.d = Desc(dt, epi, self.A.data_ptr(), self.B.data_ptr(), 0, self.bias.data_ptr(),
+                      self.R.data_ptr(), M, N, K, K, gmod * K, self.ldc, M * K, N * gmod * K, size,
+                      size, self.bias.shape[1], batch, groups, batch * M * K, K, gmod, 1,
+                      batch * size, groups * batch * M * K if dual else 0, None, None)
+
+    def run(self, kind, nb, waves=0, splits=1, what=None):
+        planes = splits if self.epi == PART else 2 if self.epi == HILO else 1
+        C = torch.full((planes, self.batch, self.rows, self.ldc), MARK, dtype=self.out, device="cuda")
+        self.d.C, self.d.splits = C.data_ptr(), splits
+        rc = launch(self.d, kind, nb, waves)
+        if rc != 0:
+            return rc
+        what = (self.M, self.N, self.groups, splits, kind, nb, waves, what)
+        assert bool((C[:, :, self.M:] == MARK).all()) and bool((C[..., self.N:] == MARK).all()), what
+        unit = UNIT[self.out] ** (2 if self.epi == HILO else 1)
+        check(C[:, :, :self.M, :self.N].double().sum(0), self.ref, unit, self.k, self.sums, what)
+        return 0
+
+
 # (M, N, K, batch, K splits): one row past and short of tiles of 128 and 256, column counts
 # that are no multiple of a tile or of 4, splits of unequal length, a single slice
 SHAPES = [(65, 96, 64, 1, 1), (127, 130, 192, 2, 3), (128, 160, 128, 1, 2), (129, 257, 320, 2, 5),
           (255, 64, 640, 1, 4), (257, 320, 512, 2, 8), (300, 33, 448, 3, 2)]
+
+
+def all_plans(dt):
+    plans = [(TILE256, 0), (TILE128, 0)] + [(MID, nb) for nb in range(1, 7)]
+    return plans + ([(TILE128, 2)] if dt != F32 else [])      # 128 x 64
 
 
 @pytest.mark.gpu
@@ -172,46 +288,30 @@ SHAPES = [(65, 96, 64, 1, 1), (127, 130, 192, 2, 3), (128, 160, 128, 1, 2), (129
 def test_every_plan_at_tile_edges(dt, epi):
     if epi == HILO and dt == F32:
         pytest.skip("two 16-bit terms")
-    f = getattr(_lib(), "_ZN6kraken19launch_gemm_plannedERKNS_8GemmDescERKNS_8GemmPlanEP12ihipStream_t")
-    f.restype = I
-    S = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[dt]
-    out = torch.float32 if epi in (RES, PART) else S
-    # rounding of the stored type (half a unit, and twice that for ties of fp32 sums); fp32
-    # sums of K products of unit-variance operands: far below 1e-5 of the result's norm
-    tol = {torch.float32: 1e-5, torch.float16: 4e-4, torch.bfloat16: 3.2e-3}[out]
-    if epi == HILO:
-        tol = {BF16: 2e-5, F16: 1e-6}[dt]     # (2^-8)^2, and (2^-11)^2 with fp32 sums
-    plans = [(TILE256, 0), (TILE128, 0)] + [(MID, nb) for nb in range(1, 7)]
-    if dt != F32:
-        plans.append((TILE128, 2))            # 128 x 64
     for M, N, K, batch, splits in SHAPES:
         if epi == HILO and N % 4:
             N += 4 - N % 4
-        g = torch.Generator(device="cuda").manual_seed(M + N + K)
-        A = torch.randn((batch, M, K), generator=g, device="cuda").to(S)
-        B = (torch.randn((batch, N, K), generator=g, device="cuda") / math.sqrt(K)).to(S)
-        bias = torch.randn((batch, M if epi == BIAS_M else N), generator=g, device="cuda")
-        R = torch.randn((batch, M, N), generator=g, device="cuda")
-        ref = torch.stack([a @ b.T for a, b in zip(A.double(), B.double())])
-        if epi != PART:
-            ref = ref + (bias.double()[:, :, None] if epi == BIAS_M else bias.double()[:, None])
-        if epi == GELU:
-            ref = torch.nn.functional.gelu(ref)
-        if epi in (RES, HILO):
-            ref = ref + R.double()
-        planes = splits if epi == PART else 2 if epi == HILO else 1
-        d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
-                 K, K, N, M * K, N * K, M * N, M * N, bias.shape[1], batch, 1, 0, 0, 1,
-                 splits if epi == PART else 1, batch * M * N, 0, None, None)
-        for kind, nb in plans:
-            C = torch.full((planes, batch, M, N), float("nan"), dtype=out, device="cuda")
-            d.C = C.data_ptr()
-            rc = f(ctypes.byref(d), ctypes.byref(Plan(kind, nb, d.splits)),
-                   P(torch.cuda.current_stream().cuda_stream or None))
-            assert rc == 0
-            torch.cuda.synchronize()
-            err = float((C.double().sum(0) - ref).norm() / ref.norm())
-            assert err <= tol, (M, N, K, batch, splits, kind, nb, err)
+        for pad in (4, 3):                    # rows that whole groups of 4 can and cannot be stored to
+            if epi == HILO and pad == 3:
+                continue
+            p = Product(dt, epi, M, N, K, batch, pad=pad)
+            for kind, nb in all_plans(dt):
+                assert p.run(kind, nb, splits=splits if epi == PART else 1, what=pad) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups,gmod", [(3, 3), (6, 3), (4, 1)])
+@pytest.mark.parametrize("epi", [RES, PART])
+@pytest.mark.parametrize("dt", [F32, BF16, F16])
+def test_k_groups_and_splits_that_begin_inside_them(dt, epi, groups, gmod):
+    """W_concat's reduction: groups of K, the weights of gmod groups used in turn (two terms: twice
+    each).  Splits of 2, 5 and 7 begin inside groups, at their borders and across the wrap."""
+    for M, N, K, batch in ((65, 100, 192, 1), (130, 68, 128, 2), (257, 132, 64, 1)):
+        p = Product(dt, epi, M, N, K, batch, groups, gmod)
+        for kind, nb in all_plans(dt):
+            for splits in (2, 5, 7) if epi == PART else (1,):
+                if splits <= K // (32 if dt == F32 else 64) * groups:
+                    assert p.run(kind, nb, splits=splits) == 0
 
 
 # a few rows: one to four blocks of 16, column counts that are no multiple of 16 or 32, steps of
@@ -227,44 +327,70 @@ FEW_ROWS = [(1, 300, 64, 2), (5, 1000, 2048, 3), (16, 64, 8192, 1), (17, 33, 320
 def test_every_few_row_plan(dt, epi, dual):
     if dt == F32 and (epi == HILO or dual) or dual and epi not in (RES, PART):
         pytest.skip("not a kernel")
-    f = getattr(_lib(), "_ZN6kraken19launch_gemm_plannedERKNS_8GemmDescERKNS_8GemmPlanEP12ihipStream_t")
-    f.restype = I
-    S = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[dt]
-    out = torch.float32 if epi in (RES, PART) else S
-    # as above
-    tol = {torch.float32: 1e-5, torch.float16: 4e-4, torch.bfloat16: 3.2e-3}[out]
-    if epi == HILO:
-        tol = {BF16: 2e-5, F16: 1e-6}[dt]
     for M, N, K, batch in FEW_ROWS:
-        if epi == PART and K < 256:        # fewer slices than splits are refused
-            continue
-        g = torch.Generator(device="cuda").manual_seed(M + N + K)
-        # two terms of A: the second one is the kernel's only where it reads two
-        A = torch.randn((2, batch, M, K), generator=g, device="cuda").to(S)
-        B = (torch.randn((batch, N, K), generator=g, device="cuda") / math.sqrt(K)).to(S)
-        bias = torch.randn((batch, N), generator=g, device="cuda")
-        R = torch.randn((batch, M, N), generator=g, device="cuda")
-        a64 = A.double().sum(0) if dual else A[0].double()
-        ref = torch.stack([a @ b.T for a, b in zip(a64, B.double())])
-        if epi != PART:
-            ref = ref + bias.double()[:, None]
-        planes = 3 if epi == PART else 2 if epi == HILO else 1
-        if epi == GELU:
-            ref = torch.nn.functional.gelu(ref)
-        if epi in (RES, HILO):
-            ref = ref + R.double()
-        d = Desc(dt, epi, A.data_ptr(), B.data_ptr(), 0, bias.data_ptr(), R.data_ptr(), M, N, K,
-                 K, K, N, M * K, N * K, M * N, M * N, N, batch, 1, 0, 0, 1, 3 if epi == PART else 1, batch * M * N,
-                 batch * M * K if dual else 0, None, None)
-        for tw, waves in [(t, w) for t in (1, 2) for w in (4, 8, 16)]:
-            C = torch.full((planes, batch, M, N), float("nan"), dtype=out, device="cuda")
-            d.C = C.data_ptr()
-            rc = f(ctypes.byref(d), ctypes.byref(Plan(SKINNY, tw, d.splits, waves)),
-                   P(torch.cuda.current_stream().cuda_stream or None))
-            if (tw, waves) not in few_row_forms(dt, M):
-                assert rc != 0                # (refused by the host: not built)
+        for groups, splits in ((1, 3), (3, 5)):
+            if epi == PART and K // (32 if dt == F32 else 64) * groups < splits:
+                continue                      # fewer slices than splits are refused
+            if groups * K > 7000 or groups > 1 and epi not in (RES, PART):
                 continue
-            assert rc == 0
-            torch.cuda.synchronize()
-            err = float((C.double().sum(0) - ref).norm() / ref.norm())
-            assert err <= tol, (M, N, K, batch, tw, waves, err)
+            p = Product(dt, epi, M, N, K, batch, groups, groups, dual=dual)
+            for tw, waves in [(t, w) for t in (1, 2) for w in (4, 8, 16)]:
+                rc = p.run(SKINNY, tw, waves, splits if epi == PART else 1)
+                # (a form that is not built is refused by the host)
+                assert (rc == 0) == ((tw, waves) in few_row_forms(dt, M)), (M, tw, waves)
+
+
+# (heads, key/value heads, head size): borders of Q, K and V inside and on the tiles of every
+# kernel; 416 and 320 columns are no multiple of 32 nb for some nb
+QKV_HEADS = [(3, 2, 32), (4, 4, 32), (3, 1, 64), (5, 2, 64), (2, 1, 128), (4, 2, 128)]
+
+
+def qkv_plans(dt, M):
+    return [(MID, nb, 0) for nb in range(1, 7)] + [(SKINNY, t, w) for t, w in few_row_forms(dt, M)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("decode", [False, True])
+@pytest.mark.parametrize("dt", [F32, BF16, F16])
+def test_qkv_columns_go_to_their_places(dt, decode):
+    """The merged projection: Q | K rows and V transposed (prefill), or Q rows and K and V at each
+    sequence's place in the cache (decode step), and nothing anywhere else."""
+    S, batch, K = TORCH[dt], 2, 192
+    rng = random.Random(3)
+    for M in (1, 7, 16, 29, 64, 70, 128, 133, 256) + (() if decode else (300,)):
+        for H, Hkv, hd in QKV_HEADS:
+            dq, dkv = H * hd, Hkv * hd
+            N = dq + 2 * dkv
+            p = Product(dt, BIAS_N, M, N, K, batch, pad=0)
+            d, cap, max_seqs = p.d, 9, M + 2
+            lens = [rng.randint(0, cap - 1) for _ in range(M)]
+            ldv = (M + 63) // 64 * 64
+            cols = dq if decode else dq + dkv
+            d.epi, d.ldc, d.sC = QKV, cols + 4, (M + 1) * (cols + 4)
+            for kind, nb, waves in qkv_plans(dt, M):
+                C = torch.full((batch, M + 1, cols + 4), MARK, dtype=S, device="cuda")
+                vt = torch.full((batch, dkv, ldv), MARK, dtype=S, device="cuda")
+                cache = torch.full((batch, 2, max_seqs, Hkv, cap, hd), MARK, dtype=S, device="cuda")
+                q = Qkv(vt.data_ptr(), dkv * ldv, cache.data_ptr() if decode else None, ldv, dq, dkv,
+                        hd, Hkv, max_seqs, cap)
+                for b, n in enumerate(lens):
+                    if decode:
+                        q.lens[b] = n
+                d.C, d.qkv, d.splits = C.data_ptr(), ctypes.addressof(q), 1
+                assert launch(d, kind, nb, waves) == 0
+                what = (M, H, Hkv, hd, kind, nb, waves)
+                got = torch.empty((batch, M, N), dtype=S, device="cuda")
+                got[..., :cols] = C[:, :M, :cols]
+                assert bool((C[:, M:] == MARK).all()) and bool((C[..., cols:] == MARK).all()), what
+                if decode:
+                    slot = torch.arange(M, device="cuda")
+                    at = torch.tensor(lens, device="cuda")
+                    rows = cache[:, :, slot, :, at]                  # [M][batch][2][Hkv][hd]
+                    got[..., dq:] = rows.permute(1, 0, 2, 3, 4).reshape(batch, M, 2 * dkv)
+                    cache[:, :, slot, :, at] = MARK
+                    assert bool((vt == MARK).all()), what
+                else:
+                    got[..., cols:] = vt[:, :, :M].transpose(1, 2)
+                    assert bool((vt[:, :, M:] == MARK).all()), what
+                assert bool((cache == MARK).all()), what
+                check(got, p.ref, UNIT[S], p.k, p.sums, what)
