@@ -22,6 +22,7 @@ import torch
 
 from oracle import kraken_oracle as O
 from paper_2408_07802_amd import synth
+from test_gemm_plans import BF16, F32, MID, QKV, TILE128, plan
 from test_gpu_prefill import DEV, TOL, build_model, f64, oracle_layers, rel_err, say, small
 
 pytestmark = pytest.mark.gpu
@@ -76,6 +77,10 @@ def prefill_then_decode(w, lens, steps=2, seed=0, affine="random", capacity=None
     out, sub = model.prefill_kv(X, cu, cache, sub_out=True)
     model.sync()
     assert torch.equal(out, out_p) and torch.equal(sub, sub_p), "prefill_kv != prefill"
+    model.poison_workspace()
+    plain, _ = model.prefill_kv(X, cu, cache)      # (another tail of the pass, the same sums)
+    model.sync()
+    assert torch.equal(plain, out), "out without sub_out != out with it"
 
     layers = [list(l) for l in oracle_layers(w, seed, affine)]
     out_o, _, kv = O.kraken_prefill(f64(X), cu, layers, wconcat(w, seed), w.n_heads,
@@ -100,7 +105,10 @@ def prefill_then_decode(w, lens, steps=2, seed=0, affine="random", capacity=None
         Xn = synth.gen_hidden(w, B, seed + 1 + step, DEV)
         model.poison_workspace()
         out_d, sub_d = model.decode(Xn, cur, cache, sub_out=True)
+        model.poison_workspace()
+        plain, _ = model.decode(Xn, cur, cache)    # (appends the same keys and values again)
         model.sync()
+        assert torch.equal(plain, out_d), "out without sub_out != out with it"
         out_do, sub_do, kv_new = O.kraken_decode(f64(Xn), cache_o, layers, wconcat(w, seed),
                                                  w.n_heads, n_kv_heads=w.kv_heads)
         check(f"step {step} out", out_d, out_do, bound)
@@ -141,12 +149,28 @@ def test_prefill_kv_then_decode_fp16_operands():
 
 @pytest.mark.parametrize("B,dtype", [(70, "bf16"), (256, "f32")])
 def test_decode_large_batches(B, dtype):
-    # 70 rows: the projections leave the few-row GEMM for the tiled one; 256: the most
-    # sequences one call takes
+    # 70 rows: the projections leave the few-row GEMM for the streaming one (tiles of 32
+    # columns); 256: the most sequences one call takes
     rng = np.random.default_rng(B)
     lens = [int(v) for v in rng.integers(1, 13 if B < 100 else 6, size=B)]
     w = small(f"dec-batch{B}-n2-l2-d128-h4", dtype=dtype)
     prefill_then_decode(w, lens, steps=1)
+
+
+# (type, N, width, heads, key/value heads, kernel of the Q | K | V projection): tiled ones, after
+# which V goes through a projection and an append of its own, and streaming tiles of more than 32
+# columns, which place keys and values themselves
+@pytest.mark.parametrize("dtype,N,d,H,Hkv,kind,nb", [
+    ("bf16", 12, 128, 4, 2, TILE128, 0), ("f32", 16, 448, 14, 14, TILE128, 0),
+    ("bf16", 16, 192, 6, 2, MID, 2), ("f32", 16, 192, 6, 2, MID, 2),
+    ("bf16", 12, 384, 12, 6, MID, 3), ("bf16", 12, 512, 16, 8, MID, 4)])
+def test_decode_batches_of_every_projection_kernel(dtype, N, d, H, Hkv, kind, nb):
+    B = 130
+    p = plan(F32 if dtype == "f32" else BF16, QKV, B, d + 2 * Hkv * (d // H), d, 1, N, 0)
+    assert (p.kind, p.nb) == (kind, nb)
+    w = small(f"dec-batch{B}-n{N}-d{d}", n_sub=N, n_layers=1, d_model=d, n_heads=H, n_kv_heads=Hkv,
+              d_ff=2 * d, dtype=dtype)
+    prefill_then_decode(w, [1 + b % 3 for b in range(B)], steps=1)
 
 
 def decode_over_standin_cache(w, lens, decode_tokens, seed=3, k_std=4.0):

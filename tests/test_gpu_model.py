@@ -23,6 +23,7 @@ import torch
 
 from oracle import kraken_oracle as O
 from paper_2408_07802_amd import synth
+from test_gemm_plans import F16, F32, RES, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -97,7 +98,11 @@ def prefill_vs_oracle(w, lens, affine="random", seed=0):
     model.poison_workspace()
     out, sub = model.prefill(X, cu, sub_out=True)
     model.sync()
+    model.poison_workspace()
+    plain, _ = model.prefill(X, cu)      # (another tail of the pass, the same sums)
+    model.sync()
     model.close()
+    assert torch.equal(plain, out), "out without sub_out != out with it"
     ref = O.stack_forward(f64(X), cu, w.arch, list(oracle_layers(w, seed, affine)), w.n_heads,
                           oracle_wc(w, seed), head_dim=w.head_size or None,
                           n_kv_heads=w.kv_heads)
@@ -174,6 +179,42 @@ def test_head_size_other_than_width_over_heads(arch):
     w = small(f"{arch}-hd128-d320", n_sub=1 if arch != "kraken" else 2, n_layers=2, d_model=320,
               n_heads=2, d_ff=640, compute="f16", arch=arch, head_size=128)
     prefill_vs_oracle(w, [150, 33])
+
+
+@pytest.mark.parametrize("arch", ["gpt", "parallel"])
+@pytest.mark.parametrize("dtype,compute", [("f32", "storage"), ("bf16", "f16")])
+def test_split_last_projection_of_the_comparison_architectures(arch, dtype, compute):
+    """Few columns and a long reduction: the last FFN-down is split, and
+    without sub_out the launch that sums its planes writes the caller's rows itself.  Prompts of
+    20 and 130 rows, then a decode step, whose row equals that of the longer prompt."""
+    w = small(f"{arch}-d256-f8192", n_sub=1, n_layers=2, d_model=256, n_heads=4, d_ff=8192,
+              dtype=dtype, compute=compute, arch=arch)
+    dt = F32 if dtype == "f32" else F16
+    for T in (2, 20, 130):
+        assert plan(dt, RES, T, 256, 8192, 1, 1, T * 256 * 4, own_sum=True).splits > 1, T
+    prefill_vs_oracle(w, [20])
+    prefill_vs_oracle(w, [100, 30])
+    lens = [40, 9]
+    cu = synth.cu_seqlens(lens)
+    model = build_model(w, cu[-1], affine="random")
+    cache = model.new_kv_cache(2, 64)
+    X = synth.gen_hidden(w, cu[-1], 0, DEV)
+    model.prefill_kv(X, cu, cache)
+    Xn = synth.gen_hidden(w, 2, 1, DEV)
+    model.poison_workspace()
+    out, sub = model.decode(Xn, lens, cache, sub_out=True)
+    model.poison_workspace()
+    plain, _ = model.decode(Xn, lens, cache)
+    model.sync()
+    model.close()
+    assert torch.equal(plain, out) and torch.equal(sub[0], out)
+    longer = [v + 1 for v in lens]
+    cu1 = synth.cu_seqlens(longer)
+    X1 = torch.cat([t for b in range(2) for t in (X[cu[b]:cu[b + 1]], Xn[b:b + 1])])
+    ref = O.stack_forward(f64(X1), cu1, arch, list(oracle_layers(w, 0, "random")), w.n_heads)
+    e = rel_err(f64(plain), ref[[c - 1 for c in cu1[1:]]])
+    say(f"[split decode] {arch} {dtype} max|err|/rms {e:.3e}")
+    assert e <= TOL[dtype]
 
 
 # --------------------------------------------------------------- token in, logits out
