@@ -148,18 +148,32 @@ def copy_probe(dev):
     torch.cuda.synchronize()
 
 
-def decode_class_bytes(w, es, B, ctx):
+def launched_work(work, prof):
+    """`work` (per kernel class) by the launches that did it: where no V projection was
+    launched, one launch computed Q, K and V (prof: name -> (ms, launches))."""
+    work = dict(work)
+    if prof["gemm_vt"][1] == 0:
+        work["gemm_qk"] += work.pop("gemm_vt")
+    return work
+
+
+def decode_class_bytes(w, es, B, ctx, merged):
     """Algorithmic HBM bytes of one decode step per kernel class: every weight matrix
     read once in the operand type (es bytes), each sequence's cached keys and values
     of ctx + 1 positions read once, the new keys and values written once, fp32
-    activations of the B rows read and written once per kernel."""
+    activations of the B rows read and written once per kernel.  merged: one launch computes
+    Q, K and V and writes the new keys and values."""
     N, L, d, F, dkv = w.n_sub, w.n_layers, w.d_model, w.d_ff, w.kv_width
     act = lambda cols: B * cols * 4
+    qk, v = d + dkv, dkv
+    if merged:
+        qk, v = qk + v, 0
+    project = lambda cols: L * N * (cols * d * es + B * d * es + B * cols * es) if cols else 0
     return {
         "ln1": L * (act(N * d) + B * N * d * es),
-        "gemm_qk": L * N * ((d + dkv) * d * es + B * d * es + B * (d + dkv) * es),
-        "gemm_vt": L * N * (dkv * d * es + B * d * es + B * dkv * es),
-        "kv_cache": L * N * B * 2 * dkv * es * 2,
+        "gemm_qk": project(qk),
+        "gemm_vt": project(v),
+        "kv_cache": 0 if merged else L * N * B * 2 * dkv * es * 2,
         "attention": L * N * (B * (ctx + 1) * 2 * dkv * es + B * (d + dkv) * es + B * d * es),
         "gemm_o": L * N * (d * d * es + B * d * es + 2 * act(d)),
         "combine_ln2": L * (2 * N * act(d) + N * B * d * es),
@@ -235,7 +249,7 @@ def bench_decode(args, w, compute):
     model.close()
 
     es = 4 if compute == "f32" else 2
-    cb = decode_class_bytes(w, es, B, ctx)
+    cb = decode_class_bytes(w, es, B, ctx, merged=prof["gemm_vt"][1] == 0)
     kernels = {}
     for name, (ms, n) in prof.items():
         if n == 0:
@@ -474,12 +488,14 @@ def main():
 
     peak = MFMA_PEAK_TFLOPS[compute]
     total_flops = sum(kraken.class_flops(cfg, k, cu) for k in range(kraken.K_COUNT))
+    work = launched_work({name: kraken.class_flops(cfg, k, cu)
+                          for k, name in enumerate(kraken.KERNEL_CLASS_NAMES)}, prof)
     kernels = {}
-    for k, name in enumerate(kraken.KERNEL_CLASS_NAMES):
+    for name in kraken.KERNEL_CLASS_NAMES:
         ms, n = prof[name]
         if n == 0:
             continue
-        fl = kraken.class_flops(cfg, k, cu)
+        fl = work[name]
         per_launch = fl / (n / args.steps) if fl else 0.0
         avg_ms = ms / n
         kernels[name] = {"ms_per_step": ms / args.steps, "launches_per_step": n // args.steps,

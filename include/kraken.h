@@ -335,15 +335,18 @@ const char* kraken_last_error(void);
  */
 enum {
   KRAKEN_K_LN1 = 0,        /* LayerNorm before MHA */
-  KRAKEN_K_GEMM_QK = 1,    /* Q,K projection */
+  KRAKEN_K_GEMM_QK = 1,    /* Q,K projection; Q,K,V where one launch computes all three (few to
+                              some hundred rows; a decode step's launch then also writes the
+                              cache), and classes 2 and, in a decode step, 10 have no launch */
   KRAKEN_K_GEMM_VT = 2,    /* V projection (written transposed) */
   KRAKEN_K_ATTN = 3,       /* causal flash attention */
   KRAKEN_K_GEMM_O = 4,     /* output projection + residual */
   KRAKEN_K_COMBINE = 5,    /* N-way sum + residual + LayerNorm before FFN (GPT-like: LN2) */
   KRAKEN_K_GEMM_UP = 6,    /* FFN up projection + GELU */
   KRAKEN_K_GEMM_DOWN = 7,  /* FFN down projection + residual */
-  KRAKEN_K_CONCAT = 8,     /* W_concat (and its operand split) */
-  KRAKEN_K_OTHER = 9,      /* input conversion, output copies, embedding, final LayerNorm */
+  KRAKEN_K_CONCAT = 8,     /* W_concat (and its operand split, and sums of K-split planes) */
+  KRAKEN_K_OTHER = 9,      /* input conversion, output copies, embedding, final LayerNorm, the last
+                              layer's sum of K-split planes (but for W_concat's 16-bit terms) */
   KRAKEN_K_KV = 10,        /* KV cache writes (kraken_prefill_kv, kraken_decode) */
   KRAKEN_K_UNEMBED = 11,   /* unembedding GEMM (kraken_forward_tokens) */
   KRAKEN_K_COUNT = 12
@@ -354,7 +357,8 @@ kraken_status kraken_profile_read(kraken_model* m, int kernel_class, double* tot
 kraken_status kraken_profile_reset(kraken_model* m);
 /* Algorithmic FLOPs (matrix products and attention, causal pairs only) of one
  * prefill over `cu_seqlens`, per kernel class: returns 0 for classes that do
- * no matrix work. */
+ * no matrix work.  V's work is KRAKEN_K_GEMM_VT's whether or not it is launched
+ * alone. */
 double kraken_class_flops(const kraken_config* cfg, int kernel_class, const int32_t* cu_seqlens,
                           int32_t num_seqs);
 

@@ -278,6 +278,25 @@ def test_forward_tokens_rejects_bad_arguments_before_the_device():
     assert L.kraken_forward_tokens(None, ids, cu, 1, None, None, None) == K().ERR_INVALID_ARG
 
 
+def test_bench_rates_count_the_work_of_a_merged_projection():
+    # where one launch computes Q, K and V its rate is that of all three; two launches keep
+    # their own
+    import bench
+    from paper_2408_07802_amd import synth
+    work = {"gemm_qk": 4.0, "gemm_vt": 2.0, "attention": 1.0}
+    two = {"gemm_qk": (1.0, 24), "gemm_vt": (1.0, 24), "attention": (1.0, 24)}
+    assert bench.launched_work(work, two) == work
+    one = dict(two, gemm_vt=(0.0, 0))
+    assert bench.launched_work(work, one) == {"gemm_qk": 6.0, "attention": 1.0}
+    w = synth.workload(synth.BENCH_WORKLOAD)
+    a, b = (bench.decode_class_bytes(w, 2, 1, 8192, merged) for merged in (False, True))
+    d, n = w.d_model, w.n_layers * w.n_sub
+    assert b["gemm_vt"] == b["kv_cache"] == 0
+    assert b["gemm_qk"] == n * 2 * (3 * d * d + d + 3 * d)        # weights, input row, results
+    # apart from V's second read of the input row and the append's copy, the step's bytes stay
+    assert sum(a.values()) - sum(b.values()) == n * 2 * (d + 4 * d)
+
+
 def test_class_flops_of_the_comparison_architectures():
     cu = [0, 128]
     for arch, N in (("gpt", 1), ("parallel", 1), ("kraken", 4)):
