@@ -49,8 +49,8 @@ COPY_PROBE_BYTES = 1 << 30
 TRAFFIC = {
     "attention": {
         "source": "paper_2408_07802_amd/csrc/attention.hip",
-        "source_sha256": "32c3b0875815dbc07b693ff4d38347e7f2acbd0c2c4729cd2b698cbbc0b5728d",
-        "read_bytes": 3283632289, "write_bytes": 269469279,
+        "source_sha256": "ed56201f8c1fbbad748e2b5981647bd1e7fd4da6fbd05301c0fdd0797f8cbeed",
+        "read_bytes": 3283220738, "write_bytes": 269468096,
         "algorithmic_bytes": 4 * 8 * 8192 * 2048 * 2,
         "profile": "profiles/hbm_traffic_n8_l24_d2048_t8192.md",
     },
@@ -58,7 +58,7 @@ TRAFFIC = {
     "gemm_up": {
         "source": "paper_2408_07802_amd/csrc/gemm_tile.hip",
         "source_sha256": "bb50799ce9199d49e4758477fb8b7b5a4d5a5f10776bcfd45f7a2477e74795c0",
-        "read_bytes": 3224320361, "write_bytes": 1073965163,
+        "read_bytes": 3224346911, "write_bytes": 1073915685,
         "algorithmic_bytes": 2 * (8 * 8192 * 2048 * 2 + 8 * 8192 * 8192) + 8 * 8192 * 4,
         "profile": "profiles/hbm_traffic_n8_l24_d2048_t8192.md",
     },
@@ -67,7 +67,7 @@ TRAFFIC = {
     "decode_attention_b1_ctx8192": {
         "source": "paper_2408_07802_amd/csrc/decode.hip",
         "source_sha256": "a5b9a13de10dd75687f70c923d1abf9d78b9c25dd45c4835a764ca8852d10fcd",
-        "read_bytes": 537723371, "write_bytes": 450560,
+        "read_bytes": 537730251, "write_bytes": 450560,
         "algorithmic_bytes": 537034752,
         "profile": "profiles/hbm_traffic_decode_n8_l24_d2048_ctx8192.md",
     },

@@ -11,9 +11,11 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Modelled time (us) of a GEMM of `tiles` workgroups, `slots` of them at a time, whose
 // reduction is `slices` 128-byte slices long: launch + rounds x (prologue and epilogue +
 // slices), a slice taking longer the fuller the round is (operand traffic, clock).  The
-// constants are a fit to measured times (fp16 / bf16: 3193 runs over 65 to 17228 rows, widths
-// 256 to 16384, 1 to 8 K splits; fp32: 850 runs): the plan with the least modelled time is on
-// average 1.5% (fp32 2%) slower than the fastest of all plans.
+// constants are a fit to measured times over 65 to 17228 rows, widths 256 to 16384, 1 to 8 K
+// splits.  On a sample of its own (random shapes, every plan timed; profiles/gemm_plans.md) the
+// plan with the least modelled time is on average 2.0% (480 shapes, fp16) and 3.6% (160, fp32)
+// slower than the fastest of all plans, half of them are the fastest; the worst are fp32 at 600 to
+// 1600 rows, where 128 x 128 tiles of a last round that is partly empty take up to 1.7 times.
 // A launch takes at least as long as its weights do at the rate the kernel streams them into LDS
 // (128 rows, weights from HBM, 4 x 4992 -> 9984 and 4992 columns: 3.5 TB/s in 128 x 128 tiles, 5.0
 // through the streaming kernel's tiles of 5 blocks of columns, 2.8 to 3.4 through 1 or 2; the same

@@ -1,5 +1,7 @@
-// Batched MFMA GEMM for 65 to a few hundred rows: C[z] = epi(A[z] B[z]^T), the shape of a
-// short prompt's or a large decode batch's projections.
+// Batched MFMA GEMM for some tens to a few hundred rows: C[z] = epi(A[z] B[z]^T), the shape of a
+// short prompt's or a large decode batch's projections.  (plan_gemm takes it from 17 rows on, or
+// where the few-row kernel ends, up to 512, up to 2560 where 128 x 128 tiles would leave CUs
+// idle; fp32 there at any number of rows.)
 //
 // Every weight (B) element is used M times only, so the launch is bound by streaming the
 // weights, and what matters is how many weight bytes are in flight.  The tiled kernel keeps
@@ -12,7 +14,9 @@
 // Measured with weights from HBM, 128 rows, fp16 (before: the 128 x 128 tiled kernel): 4 x
 // 4992 -> 9984 columns 115 -> 78 us (5.1 TB/s), 4 x 1280 -> 3072 21 -> 14 us; with K splits,
 // 4 x 4992 -> 4992 73 -> 46 us, 4 x 2496 -> 1280 36 -> 11 us, a W_concat of 39936 -> 4992
-// 491 -> 80 us.  With every wave loading and multiplying, one ring for both operands and five
+// 491 -> 80 us (two terms of 19968: its 199 MB of weights come twice, 2.5 TB/s of them once).
+// Within a layer (counters and times in profiles/short_prompt_kernels.md) the first of these reads
+// 417 MB in 97 us.  With every wave loading and multiplying, one ring for both operands and five
 // slices on their way: 4 x 1280 -> 3072 16 us, a W_concat of 10240 -> 1280 13.9 (now 12.8) us.
 //
 // 8 waves, two per SIMD: 4 loaders only issue the direct-to-LDS loads (two waves for each
