@@ -419,15 +419,25 @@ int64_t planes_at(const Dims& D, DType dt, int T, int Tmax) {
   return n;
 }
 
-// The same over all T up to Tmax.  Past 128 rows plans are made once per 16: within such a block
-// every kernel has the same tiles, and the cost and limit of the planes only grow with T, so the
-// first row has the most splits.
+// The same over all T up to Tmax.  The rows between two edges of a kernel's tiles (and of the
+// few-row kernel's forms) have the same tiles, and the cost and limit of the planes only grow with
+// T, so the first of them has the most splits and bounds them all.  Where the bound could be more
+// than is known already, plans are made for every row, past 128 rows for one in 16.  (From the
+// largest T down, where few splits are left; plans for all rows took a model 0.15 to 0.35 ms.)
 int64_t planes_upto(const Dims& D, DType dt, int Tmax) {
   const int64_t room = plane_room(D, Tmax);
+  auto bound = [&](int T, int last) { return planes_at(D, dt, T, Tmax) / T * last; };
   int64_t n = 0;
-  for (int T = 1; T <= std::min(Tmax, 128); ++T) n = std::max(n, planes_at(D, dt, T, Tmax));
-  for (int T = 129; T <= Tmax && 2 * (int64_t)T * D.d <= room; T += 16)
-    n = std::max(n, planes_at(D, dt, T, Tmax) / T * std::min(T + 15, Tmax));
+  for (int last = Tmax; last >= 1;) {
+    const int first = last > 64 ? std::max(65, (last - 1) / 128 * 128 + 1)
+                      : last > 32 ? 33 : last > 16 ? 17 : last > 1 ? 2 : 1;
+    if (2 * (int64_t)first * D.d <= room && bound(first, last) > n) {
+      const int step = first < 128 ? 1 : 16;
+      for (int T = first; T <= last; T += step)
+        n = std::max(n, bound(T, std::min(T + step - 1, last)));
+    }
+    last = first - 1;
+  }
   return std::min(n, room);
 }
 
@@ -447,7 +457,7 @@ size_t carve_workspace(kraken_model* m, void* base) {
   m->act = c.take(N * T * dp * es);
   m->qk = c.take(N * T * (dq + dkv) * es);
   m->o = c.take(N * T * std::max(dq, dkv) * es);
-  m->part_elems = planes_upto(D, m->dt, m->Tmax);
+  if (!base) m->part_elems = planes_upto(D, m->dt, m->Tmax);   // (the pass that counts bytes)
   m->part = (float*)c.take(m->part_elems * sizeof(float));
   // vt and g stay adjacent and last: a decode step keeps its attention partials there
   m->vt = c.take(N * dkv * (size_t)vt_ld(m->Tmax) * es);
