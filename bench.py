@@ -121,11 +121,14 @@ def step_stats(per_step_ms):
             "min": v[0], "p90": v[min(n - 1, int(math.ceil(0.9 * n)) - 1)], "max": v[-1]}
 
 
-def traffic_of(kernel):
+def traffic_of(kernel, w, compute):
     """Measured HBM traffic of `kernel` per launch: (read + write bytes, detail), or
-    (None, None) when no counter run exists for the current source of the kernel."""
+    (None, None) when no counter run exists for the current source of the kernel, or for the
+    workload and operand type (the runs are of the default ones)."""
+    from paper_2408_07802_amd import synth
+
     t = TRAFFIC.get(kernel)
-    if not t:
+    if not t or w.name != synth.BENCH_WORKLOAD or compute != "f16":
         return None, None
     with open(os.path.join(ROOT, t["source"]), "rb") as f:
         if hashlib.sha256(f.read()).hexdigest() != t["source_sha256"]:
@@ -285,8 +288,8 @@ def bench_decode(args, w, compute):
         "hbm_util_pct": 100.0 * total_bytes / (ms_per_step * 1e-3) / (HBM_PEAK_GBS * 1e9),
         "roofline": {"bound": "hbm", "kernel": dominant, "achieved": dk["gbs"],
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dk["gbs"] / HBM_PEAK_GBS,
-                     "traffic": traffic_of(f"decode_{dominant}_b{B}_ctx{ctx}")[0],
-                     "traffic_detail": traffic_of(f"decode_{dominant}_b{B}_ctx{ctx}")[1],
+                     "traffic": traffic_of(f"decode_{dominant}_b{B}_ctx{ctx}", w, compute)[0],
+                     "traffic_detail": traffic_of(f"decode_{dominant}_b{B}_ctx{ctx}", w, compute)[1],
                      "avg_launch_ms": dk["avg_launch_ms"],
                      "launches_per_step": dk["launches_per_step"]},
         "kernels": kernels,
@@ -538,8 +541,8 @@ def main():
         "algorithmic_tflop_per_step": total_flops / 1e12,
         "roofline": {"bound": "mfma", "kernel": dominant,
                      "achieved": dk["tflops"], "peak": peak, "unit": "TFLOP/s",
-                     "frac": dk["tflops"] / peak, "traffic": traffic_of(dominant)[0],
-                     "traffic_detail": traffic_of(dominant)[1],
+                     "frac": dk["tflops"] / peak, "traffic": traffic_of(dominant, w, compute)[0],
+                     "traffic_detail": traffic_of(dominant, w, compute)[1],
                      "avg_launch_ms": dk["avg_launch_ms"],
                      "launches_per_step": dk["launches_per_step"]},
         "kernels": kernels,
